@@ -8,6 +8,7 @@
 // a per-block scan (tile sums, scan of tile sums, local scans) and a scatter.
 #include <vector>
 
+#include "device.hpp"
 #include "graph.hpp"
 
 namespace csbfs {
@@ -152,9 +153,15 @@ __global__ void k_directory(const int32_t *row_ptr, int64_t R, int64_t W, int64_
 
 // deg[u] = adjacency entries of u over all blocks of its column; big[i] +=
 // the expansion-queue items that the rows of block-row i would need if every
-// row were expanded at once (the capacity of processor i's chunk queue).
-__global__ void k_degree(const int32_t *row_ptr, int64_t R, int32_t P, int64_t n, int32_t *deg,
-                         unsigned long long *big_items) {
+// row were expanded at once (the capacity of processor i's chunk queue). The
+// sums go to memory once per workgroup: device-scope atomics on one address
+// are serialized, and one per wave was most of this kernel's time (scale 20:
+// 269 us, now 46 us).
+__global__ __launch_bounds__(kThreads) void k_degree(const int32_t *row_ptr, int64_t R, int32_t P, int64_t n,
+                                                     int32_t *deg, unsigned long long *big_items) {
+    __shared__ unsigned long long big[64];  // P <= 64
+    if (threadIdx.x < 64) big[threadIdx.x] = 0;
+    __syncthreads();
     for (int64_t base = blockIdx.x * (int64_t)blockDim.x; base < n;
          base += (int64_t)gridDim.x * blockDim.x) {
         const int64_t u = base + threadIdx.x;
@@ -162,40 +169,46 @@ __global__ void k_degree(const int32_t *row_ptr, int64_t R, int32_t P, int64_t n
         const int64_t j = ok ? u / R : 0, ul = ok ? u - j * R : 0;
         int32_t d = 0;
         for (int32_t i = 0; i < P; ++i) {
-            unsigned long long items = 0;
-            if (ok) {
-                const int32_t *rp = row_ptr + ((int64_t)i * P + j) * (R + 1) + ul;
-                const int32_t len = rp[1] - rp[0];
-                d += len;
-                if (len > kBigRow) items = (len + kBigChunk - 1) / kBigChunk;
-            }
-            for (int s = 32; s > 0; s >>= 1) items += __shfl_xor(items, s, 64);
-            if ((threadIdx.x & 63) == 0 && items) atomicAdd(&big_items[i], items);
+            if (!ok) continue;
+            const int32_t *rp = row_ptr + ((int64_t)i * P + j) * (R + 1) + ul;
+            const int32_t len = rp[1] - rp[0];
+            d += len;
+            if (len > kBigRow) atomicAdd(&big[i], (unsigned long long)((len + kBigChunk - 1) / kBigChunk));
         }
         if (ok) deg[u] = d;
     }
+    __syncthreads();
+    if (threadIdx.x < P && big[threadIdx.x]) atomicAdd(&big_items[threadIdx.x], big[threadIdx.x]);
 }
 
 // Consistency of a built graph: the largest column id (must be below R) and
-// the degree total (must equal nnz).
-__global__ void k_check(const uint32_t *col, int64_t nnz, const int32_t *deg, int64_t n,
-                        unsigned long long *out) {
+// the degree total (must equal nnz). One pair of atomics per workgroup (one
+// per wave took 392 us of atomics on two addresses at scale 20; now 64).
+__global__ __launch_bounds__(kThreads) void k_check(const uint32_t *col, int64_t nnz, const int32_t *deg, int64_t n,
+                                                    unsigned long long *out) {
+    __shared__ uint32_t wmax[kThreads / 64];
     uint32_t mx = 0;
     unsigned long long ds = 0;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < nnz; k += stride)
-        mx = col[k] > mx ? col[k] : mx;
-    for (int64_t u = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; u < n; u += stride)
-        ds += (unsigned long long)deg[u];
+    const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    const int64_t quads = nnz / 4;  // col starts at a multiple of 256 bytes
+    for (int64_t k = t; k < quads; k += stride) {
+        const uint4 c = reinterpret_cast<const uint4 *>(col)[k];
+        mx = max(max(max(mx, c.x), max(c.y, c.z)), c.w);
+    }
+    for (int64_t k = quads * 4 + t; k < nnz; k += stride) mx = max(mx, col[k]);
+    for (int64_t u = t; u < n; u += stride) ds += (unsigned long long)deg[u];
     for (int d = 32; d > 0; d >>= 1) {
-        const uint32_t o = __shfl_xor(mx, d, 64);
-        mx = o > mx ? o : mx;
+        mx = max(mx, (uint32_t)__shfl_xor(mx, d, 64));
         ds += __shfl_xor(ds, d, 64);
     }
-    if ((threadIdx.x & 63) == 0) {
+    if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = mx;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < kThreads / 64; ++w) mx = max(mx, wmax[w]);
         atomicMax(&out[0], (unsigned long long)mx);
-        if (ds) atomicAdd(&out[1], ds);
     }
+    block_add<kThreads / 64>(ds, &out[1]);
 }
 
 __global__ void k_count_m(const int32_t *level, const int32_t *deg, int64_t n,
@@ -212,30 +225,99 @@ __global__ void k_count_m(const int32_t *level, const int32_t *deg, int64_t n,
 // global ids: each block row is already in decreasing order and block j
 // holds the ids of R_j, so the merged row is in decreasing order. The row's
 // first two ids are also kept beside each other per vertex (head; 0xFFFFFFFF
-// where the row is shorter), so a pull can test them without the row. One
-// thread per vertex (setup only).
-__global__ void k_pull_fill(const int32_t *row_ptr, const int64_t *col_base, const uint32_t *col,
-                            int64_t R, int32_t P, int64_t n, const int64_t *pull_off, uint32_t *pull_col,
-                            uint32_t *head) {
-    for (int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; v < n;
-         v += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t i = v / R, vl = v - i * R;
-        const int64_t d0 = pull_off[v];
-        int64_t d = d0;
-        uint32_t h[2] = {0xFFFFFFFFu, 0xFFFFFFFFu};
+// where the row is shorter), so a pull can test them without the row.
+//
+// A plain copy of nnz ids, bound by memory as long as no lane follows a hub's
+// row alone: a wavefront takes 64 vertices of one processor and, block after
+// block, spreads the entries of their 64 rows evenly over its lanes; rows
+// above kLongRow entries, which would hold such a wave for milliseconds, are
+// copied by whole workgroups (k_pull_long) from the sort's queues. Scale 20,
+// 4 x 4: one thread per vertex took 25.97 ms for the 33.5M entries (its
+// time was the largest hub's row), the two kernels 0.15 ms (2.1 TB/s).
+__device__ __forceinline__ void put_id(uint32_t id, int64_t pos, int64_t first, int64_t v, uint32_t *pull_col,
+                                       uint32_t *head) {
+    pull_col[pos] = id;
+    if (pos - first < 2) head[2 * v + (pos - first)] = id;
+}
+
+__global__ __launch_bounds__(kThreads) void k_pull_fill(const int32_t *row_ptr, const int64_t *col_base,
+                                                        const uint32_t *col, int64_t R, int32_t P, int64_t n,
+                                                        const int64_t *pull_off, uint32_t *pull_col,
+                                                        uint32_t *head) {
+    constexpr int kUn = 4;  // entries in flight per lane
+    const int lane = threadIdx.x & 63;
+    const int64_t wave = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
+    const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
+    for (int64_t g = wave; g < n / 64; g += nwaves) {
+        const int64_t v = (g << 6) + lane, i = (g << 6) / R, vl = v - i * R;  // R is a multiple of 64
+        const int64_t first = pull_off[v];
+        const int64_t deg = pull_off[v + 1] - first;
+        for (int64_t k = deg; k < 2; ++k) head[2 * v + k] = 0xFFFFFFFFu;
+        int64_t d = first;
         for (int32_t j = P - 1; j >= 0; --j) {
             const int64_t b = (int64_t)j * P + i;
             const int32_t *rp = row_ptr + b * (R + 1) + vl;
+            const int32_t rs = rp[0], len = rp[1] - rs;
+            const int32_t mine = len > kLongRow ? 0 : len;
+            const int32_t incl = wave_incl_scan_i32(mine);
+            const int32_t total = __shfl(incl, 63, 64), excl = incl - mine;
             const uint32_t *src = col + col_base[b];
             const uint32_t base = (uint32_t)(j * R);
-            for (int32_t e = rp[0]; e < rp[1]; ++e) {
-                const uint32_t id = base + src[e];
-                if (d - d0 < 2) h[d - d0] = id;
-                pull_col[d++] = id;
+            for (int32_t e0 = 0; e0 < total; e0 += 64 * kUn) {
+                uint32_t id[kUn];
+                int64_t at[kUn], f[kUn];
+                int o[kUn];
+#pragma unroll
+                for (int k = 0; k < kUn; ++k) {
+                    const int32_t e = min(e0 + 64 * k + lane, total - 1);
+                    o[k] = owner_lane(excl, e);
+                    const int32_t x = e - __shfl(excl, o[k], 64);
+                    id[k] = base + src[__shfl(rs, o[k], 64) + x];
+                    at[k] = shfl64(d, o[k]) + x;
+                    f[k] = shfl64(first, o[k]);
+                }
+#pragma unroll
+                for (int k = 0; k < kUn; ++k)
+                    if (e0 + 64 * k + lane < total) put_id(id[k], at[k], f[k], (g << 6) + o[k], pull_col, head);
+            }
+            d += len;
+        }
+    }
+}
+
+// The rows above kLongRow entries (two queues of row numbers b * R + u).
+__global__ __launch_bounds__(kThreads) void k_pull_long(const int32_t *row_ptr, const int64_t *col_base,
+                                                        const uint32_t *col, int64_t R, int32_t P,
+                                                        const int64_t *pull_off, uint32_t *pull_col, uint32_t *head,
+                                                        LongRows q) {
+    constexpr int kUn = 4;
+    const int64_t n0 = (int64_t)q.count[0] < q.cap[0] ? (int64_t)q.count[0] : q.cap[0];
+    const int64_t n1 = (int64_t)q.count[1] < q.cap[1] ? (int64_t)q.count[1] : q.cap[1];
+    // the longest rows first
+    for (int64_t k = blockIdx.x; k < n0 + n1; k += gridDim.x) {
+        const int64_t row = k < n1 ? q.rows[1][k] : q.rows[0][k - n1];
+        const int64_t b = row / R, vl = row - b * R;
+        const int32_t j = (int32_t)(b / P), i = (int32_t)(b - (int64_t)j * P);
+        const int64_t v = (int64_t)i * R + vl, first = pull_off[v];
+        int64_t d = first;
+        for (int32_t jj = P - 1; jj > j; --jj) {
+            const int32_t *rp = row_ptr + ((int64_t)jj * P + i) * (R + 1) + vl;
+            d += rp[1] - rp[0];
+        }
+        const int32_t *rp = row_ptr + b * (R + 1) + vl;
+        const int32_t rs = rp[0], len = rp[1] - rs;
+        const uint32_t *src = col + col_base[b] + rs;
+        const uint32_t base = (uint32_t)(j * R);
+        for (int32_t e0 = threadIdx.x; e0 < len; e0 += kUn * kThreads) {
+            uint32_t id[kUn];
+#pragma unroll
+            for (int u = 0; u < kUn; ++u) id[u] = src[min(e0 + u * kThreads, len - 1)];
+#pragma unroll
+            for (int u = 0; u < kUn; ++u) {
+                const int32_t e = e0 + u * kThreads;
+                if (e < len) put_id(base + id[u], d + e, first, v, pull_col, head);
             }
         }
-        head[2 * v] = h[0];
-        head[2 * v + 1] = h[1];
     }
 }
 
@@ -244,13 +326,6 @@ __global__ void k_live(const int32_t *deg, int64_t n, uint64_t *live) {
     const int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     const uint64_t b = __ballot(v < n && deg[v] > 0);
     if ((threadIdx.x & 63) == 0 && v < n) live[v >> 6] = b;
-}
-
-unsigned grid_for(int64_t items, int64_t per_block, unsigned cap = 65536) {
-    int64_t g = (items + per_block - 1) / per_block;
-    if (g < 1) g = 1;
-    if (g > cap) g = cap;
-    return (unsigned)g;
 }
 
 constexpr int kMiscWords = 64;  // build flags and counters: err, sort queue counts, check, big items
@@ -366,7 +441,7 @@ extern "C" int csbfs_graph_build_into(const int64_t *src, const int64_t *dst, in
     CSBFS_HIP(hipMemsetAsync(cnt, 0, sizeof(int32_t) * B * R, st));
     CSBFS_HIP(hipMemsetAsync(misc, 0, sizeof(unsigned long long) * (kMiscWords + p), st));
     if (n_tuples > 0) {
-        hipLaunchKernelGGL(k_count, dim3(grid_for(n_tuples, kThreads)), dim3(kThreads), 0, st, src,
+        hipLaunchKernelGGL(k_count, dim3(grid_for(n_tuples, kThreads, 65536)), dim3(kThreads), 0, st, src,
                            dst, n_tuples, n, R, p, cnt, err);
         CSBFS_HIP(hipGetLastError());
     }
@@ -398,7 +473,7 @@ extern "C" int csbfs_graph_build_into(const int64_t *src, const int64_t *dst, in
                        ntile, (const long long *)sums, g->row_ptr);
     CSBFS_HIP(hipGetLastError());
     if (n_tuples > 0) {
-        hipLaunchKernelGGL(k_scatter, dim3(grid_for(n_tuples, kThreads)), dim3(kThreads), 0, st,
+        hipLaunchKernelGGL(k_scatter, dim3(grid_for(n_tuples, kThreads, 65536)), dim3(kThreads), 0, st,
                            src, dst, n_tuples, R, p, cnt, (const int64_t *)g->col_base, g->col);
         CSBFS_HIP(hipGetLastError());
     }
@@ -407,24 +482,28 @@ extern "C" int csbfs_graph_build_into(const int64_t *src, const int64_t *dst, in
     rc = sort_rows_desc(g->col, g->pull_col, g->row_ptr, g->col_base, R, p, total,
                         (int64_t *)(sm + L.queues), qcount, err, st);
     if (rc) return rc;
-    hipLaunchKernelGGL(k_directory, dim3(grid_for(B * W * 64, kThreads)), dim3(kThreads), 0, st,
+    hipLaunchKernelGGL(k_directory, dim3(grid_for(B * W * 64, kThreads, 65536)), dim3(kThreads), 0, st,
                        (const int32_t *)g->row_ptr, R, W, B, g->dir);
     CSBFS_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_degree, dim3(grid_for(n, kThreads)), dim3(kThreads), 0, st,
+    hipLaunchKernelGGL(k_degree, dim3(grid_for(n, kThreads, 4096)), dim3(kThreads), 0, st,
                        (const int32_t *)g->row_ptr, R, p, n, g->deg, big);
     CSBFS_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_live, dim3(grid_for(n, 256, 1u << 30)), dim3(256), 0, st, (const int32_t *)g->deg, n,
+    hipLaunchKernelGGL(k_live, dim3(grid_for(n, 256, 1 << 30)), dim3(256), 0, st, (const int32_t *)g->deg, n,
                        g->live);
     CSBFS_HIP(hipGetLastError());
     // never hand the search a column id outside its block or a lost entry
-    hipLaunchKernelGGL(k_check, dim3(4096), dim3(kThreads), 0, st, (const uint32_t *)g->col, total,
+    hipLaunchKernelGGL(k_check, dim3(2048), dim3(kThreads), 0, st, (const uint32_t *)g->col, total,
                        (const int32_t *)g->deg, n, chk);
     CSBFS_HIP(hipGetLastError());
     rc = degree_offsets(g->deg, n, g->pull_off, (int64_t *)(sm + L.scan), st);
     if (rc) return rc;
-    hipLaunchKernelGGL(k_pull_fill, dim3(grid_for(n, kThreads)), dim3(kThreads), 0, st,
+    hipLaunchKernelGGL(k_pull_fill, dim3(grid_for(n, kThreads, 65536)), dim3(kThreads), 0, st,
                        (const int32_t *)g->row_ptr, (const int64_t *)g->col_base, (const uint32_t *)g->col, R, p,
                        n, (const int64_t *)g->pull_off, g->pull_col, g->head);
+    CSBFS_HIP(hipGetLastError());
+    hipLaunchKernelGGL(k_pull_long, dim3(2048), dim3(kThreads), 0, st, (const int32_t *)g->row_ptr,
+                       (const int64_t *)g->col_base, (const uint32_t *)g->col, R, p, (const int64_t *)g->pull_off,
+                       g->pull_col, g->head, sort_long_rows((const int64_t *)(sm + L.queues), qcount, total));
     CSBFS_HIP(hipGetLastError());
     std::vector<unsigned long long> tail(kMiscWords + p);
     int64_t pull_total = -1;

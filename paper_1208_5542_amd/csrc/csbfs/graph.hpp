@@ -72,7 +72,16 @@ namespace csbfs {
 int graph_device_check(const csbfs_graph *g);
 // Sort every block row (descending target id) in place; tmp has nnz entries
 // of scratch, queues and q_count come from the build scratch.
+// Rows above kLongRow entries are sorted (and copied into the pull layout) by
+// whole workgroups; the sort leaves their numbers b * R + u in two queues.
+constexpr int kLongRow = 1024;
+struct LongRows {
+    const int64_t *rows[2];
+    const unsigned long long *count;  // [2]
+    int64_t cap[2];
+};
 int64_t sort_queue_cap(int64_t nnz, int which);
+LongRows sort_long_rows(const int64_t *queues, const unsigned long long *q_count, int64_t nnz);
 int sort_rows_desc(uint32_t *col, uint32_t *tmp, const int32_t *row_ptr, const int64_t *col_base, int64_t R,
                    int32_t P, int64_t nnz, int64_t *queues, unsigned long long *q_count, int32_t *err,
                    hipStream_t st);

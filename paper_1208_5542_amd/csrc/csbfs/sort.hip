@@ -10,9 +10,11 @@
 //   L <= 32         one thread: bitonic network in registers (8 or 32 slots)
 //   33 .. 1024      one wavefront: bitonic network over the row in LDS
 //   1025 .. 16384   one workgroup: bitonic network over the row in LDS
-//   > 16384         one workgroup: least-significant-bit-first radix sort,
-//                   one stable split per bit (ones first), ping-ponging
-//                   between the row and the same range of a temp buffer
+//   > 16384         one workgroup: radix sort, 4 bits per stable pass, least
+//                   significant digit first, ping-ponging between the row
+//                   and the same range of a temp buffer
+// The two workgroup classes are a few rows each, so their time is that of
+// their longest row: they run 1024 threads per row.
 // Keys in the networks are id + 1 with 0 as padding, so padding sorts last.
 #include "graph.hpp"
 #include "device.hpp"
@@ -21,10 +23,12 @@ namespace csbfs {
 namespace {
 
 constexpr int kSortThreads = 256;
-constexpr int kWaveRow = 1024;     // longest row of the wavefront class
+constexpr int kWaveRow = kLongRow;  // longest row of the wavefront class (1024)
 constexpr int kBlockRow = 16384;   // longest row of the workgroup class
-constexpr int kRadixItems = 16;    // elements per thread per radix chunk
-constexpr int kRadixChunk = kSortThreads * kRadixItems;
+constexpr int kLongThreads = 1024;  // threads per row of the workgroup classes
+constexpr int kRadixBits = 4;
+constexpr int kRadixItems = 8;      // elements per thread per radix chunk
+constexpr int kRadixChunk = kLongThreads * kRadixItems;
 
 __device__ __forceinline__ void cas_desc(uint32_t &a, uint32_t &b) {
     // after the call a >= b
@@ -183,7 +187,9 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_wave(SortArgs a) {
     }
 }
 
-__global__ __launch_bounds__(kSortThreads) void k_sort_block(SortArgs a) {
+// 64 KiB of LDS: two workgroups of 16 waves per CU. Scale 20, 4 x 4: 1475 us
+// with 256 threads per row, 744 us now.
+__global__ __launch_bounds__(kLongThreads) void k_sort_block(SortArgs a) {
     __shared__ uint32_t s[kBlockRow];
     const int64_t count = (int64_t)a.q_count[1] < a.cap_block ? (int64_t)a.q_count[1] : a.cap_block;
     for (int64_t q = blockIdx.x; q < count; q += gridDim.x) {
@@ -198,82 +204,87 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_block(SortArgs a) {
     }
 }
 
-__device__ int block_sum_i32(int v) {
-    __shared__ int red[kSortThreads / 64];
-    for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d, 64);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-    __syncthreads();
-    int t = 0;
-    for (int k = 0; k < kSortThreads / 64; ++k) t += red[k];
-    __syncthreads();
-    return t;
-}
-
-__device__ int block_excl_i32(int v, int *total) {
-    __shared__ int ws[kSortThreads / 64];
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    const int incl = wave_incl_scan_i32(v);
-    if (lane == 63) ws[wid] = incl;
-    __syncthreads();
-    int before = 0, tot = 0;
-    for (int k = 0; k < kSortThreads / 64; ++k) {
-        if (k < wid) before += ws[k];
-        tot += ws[k];
-    }
-    __syncthreads();
-    *total = tot;
-    return before + incl - v;
-}
-
-// Rows above kBlockRow entries: one stable split per key bit, least
-// significant first, ones before zeros (so the result is descending).
-__global__ __launch_bounds__(kSortThreads) void k_sort_radix(SortArgs a) {
+// Rows above kBlockRow entries: a stable pass per digit of kRadixBits bits,
+// least significant first, larger digits first (so the result is
+// descending). The digit totals of all passes are counted in one read of the
+// row, as no pass changes them. In a pass a wave takes kRadixItems runs of 64
+// consecutive elements of its part of the chunk; four ballots give every
+// lane the elements of its wave that share its digit, and lane d keeps the
+// count of digit d, so ranks need no atomics and LDS holds only the waves'
+// counts. Scale 20 (four rows of about 35 000): 860 us with one pass per bit
+// and 256 threads, 245 us now.
+__global__ __launch_bounds__(kLongThreads) void k_sort_radix(SortArgs a) {
+    constexpr int kDigits = 1 << kRadixBits, kWaves = kLongThreads / 64;
+    constexpr int kMaxPass = 32 / kRadixBits;
+    __shared__ unsigned long long total[kMaxPass][kDigits];
+    __shared__ int32_t wcnt[kWaves][kDigits];
     const int64_t count = (int64_t)a.q_count[2] < a.cap_radix ? (int64_t)a.q_count[2] : a.cap_radix;
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    const int passes = (a.key_bits + kRadixBits - 1) / kRadixBits;
+    // lanes of this wave whose digit equals d (their digits in dig, lanes ok)
+    auto same = [](int dig, bool ok, int d) {
+        uint64_t m = __ballot(ok);
+#pragma unroll
+        for (int b = 0; b < kRadixBits; ++b) {
+            const uint64_t bal = __ballot((dig >> b) & 1);
+            m &= (d >> b) & 1 ? bal : ~bal;
+        }
+        return m;
+    };
     for (int64_t q = blockIdx.x; q < count; q += gridDim.x) {
         int64_t start, len;
         row_range(a, a.q_radix[q], start, len);
         uint32_t *from = a.col + start, *to = a.tmp + start;
-        for (int bit = 0; bit < a.key_bits; ++bit) {
-            // ones in the whole row
-            int ones = 0;
-            for (int64_t c = 0; c < len; c += kRadixChunk)
-                for (int k = 0; k < kRadixItems; ++k) {
-                    const int64_t e = c + (int64_t)threadIdx.x * kRadixItems + k;
-                    if (e < len) ones += (from[e] >> bit) & 1u;
-                }
-            const int64_t total_ones = block_sum_i32(ones);
-            int64_t ones_done = 0, zeros_done = 0;
-            for (int64_t c = 0; c < len; c += kRadixChunk) {
-                const int64_t e0 = c + (int64_t)threadIdx.x * kRadixItems;
-                uint32_t v[kRadixItems];
-                int mine = 0, have = 0;
+        for (int k = threadIdx.x; k < kMaxPass * kDigits; k += kLongThreads) (&total[0][0])[k] = 0;
+        __syncthreads();
+        {
+            unsigned long long mine[kMaxPass] = {};
+            for (int64_t e0 = (int64_t)wid * 64; e0 < len; e0 += kLongThreads) {
+                const bool ok = e0 + lane < len;
+                const uint32_t v = ok ? ~from[e0 + lane] : 0u;
 #pragma unroll
-                for (int k = 0; k < kRadixItems; ++k) {
-                    v[k] = 0;
-                    if (e0 + k < len) {
-                        v[k] = from[e0 + k];
-                        mine += (v[k] >> bit) & 1u;
-                        ++have;
-                    }
-                }
-                int chunk_ones;
-                const int ones_before = block_excl_i32(mine, &chunk_ones);
-                const int64_t chunk_len = len - c < kRadixChunk ? len - c : kRadixChunk;
-                // zeros before this thread's items in the chunk
-                int64_t o = ones_done + ones_before;
-                int64_t z = total_ones + zeros_done + ((int64_t)threadIdx.x * kRadixItems - ones_before);
-#pragma unroll
-                for (int k = 0; k < kRadixItems; ++k) {
-                    if (k < have) {
-                        if ((v[k] >> bit) & 1u)
-                            to[o++] = v[k];
-                        else
-                            to[z++] = v[k];
-                    }
-                }
-                ones_done += chunk_ones;
-                zeros_done += chunk_len - chunk_ones;
+                for (int s = 0; s < kMaxPass; ++s)
+                    if (s < passes)
+                        mine[s] += __popcll(same((int)(v >> (s * kRadixBits)) & (kDigits - 1), ok, lane & (kDigits - 1)));
             }
+            if (lane < kDigits)
+                for (int s = 0; s < passes; ++s) atomicAdd(&total[s][lane], mine[s]);
+        }
+        __syncthreads();
+        for (int s = 0; s < passes; ++s) {
+            // lane d: where digit d's next element goes
+            int64_t next = 0;
+            for (int d = 0; d < (lane & (kDigits - 1)); ++d) next += (int64_t)total[s][d];
+            for (int64_t c = 0; c < len; c += kRadixChunk) {
+                const int64_t e0 = c + (int64_t)wid * 64 * kRadixItems + lane;
+                uint32_t v[kRadixItems];
+                int32_t cnt = 0;
+#pragma unroll
+                for (int k = 0; k < kRadixItems; ++k) v[k] = e0 + 64 * k < len ? from[e0 + 64 * k] : 0u;
+#pragma unroll
+                for (int k = 0; k < kRadixItems; ++k)
+                    cnt += __popcll(same((int)(~v[k] >> (s * kRadixBits)) & (kDigits - 1), e0 + 64 * k < len,
+                                         lane & (kDigits - 1)));
+                if (lane < kDigits) wcnt[wid][lane] = cnt;
+                __syncthreads();
+                int64_t at = next;
+                for (int w = 0; w < kWaves; ++w) {
+                    const int32_t x = wcnt[w][lane & (kDigits - 1)];
+                    next += x;
+                    if (w < wid) at += x;
+                }
+#pragma unroll
+                for (int k = 0; k < kRadixItems; ++k) {
+                    const bool ok = e0 + 64 * k < len;
+                    const int dig = (int)(~v[k] >> (s * kRadixBits)) & (kDigits - 1);
+                    const uint64_t peers = same(dig, ok, dig);
+                    const int64_t pos = shfl64(at, dig) + __popcll(peers & ((1ull << lane) - 1));
+                    if (ok) to[pos] = v[k];
+                    at += __popcll(same(dig, ok, lane & (kDigits - 1)));
+                }
+                __syncthreads();
+            }
+            __threadfence_block();
             __syncthreads();
             uint32_t *t = from;
             from = to;
@@ -369,6 +380,18 @@ int64_t sort_queue_cap(int64_t nnz, int which) {
     return nnz / (above + 1) + 1;
 }
 
+LongRows sort_long_rows(const int64_t *queues, const unsigned long long *q_count, int64_t nnz) {
+    LongRows q{};
+    const int64_t *at = queues + sort_queue_cap(nnz, 0);
+    for (int k = 0; k < 2; ++k) {
+        q.rows[k] = at;
+        q.cap[k] = sort_queue_cap(nnz, k + 1);
+        at += q.cap[k];
+    }
+    q.count = q_count + 1;
+    return q;
+}
+
 int64_t scan_tiles(int64_t n) { return (n + kScanTile - 1) / kScanTile; }
 
 int sort_rows_desc(uint32_t *col, uint32_t *tmp, const int32_t *row_ptr, const int64_t *col_base, int64_t R,
@@ -398,9 +421,9 @@ int sort_rows_desc(uint32_t *col, uint32_t *tmp, const int32_t *row_ptr, const i
     CSBFS_HIP(hipGetLastError());
     hipLaunchKernelGGL(k_sort_wave, dim3(4096), dim3(kSortThreads), 0, st, a);
     CSBFS_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_sort_block, dim3(2048), dim3(kSortThreads), 0, st, a);
+    hipLaunchKernelGGL(k_sort_block, dim3(1024), dim3(kLongThreads), 0, st, a);
     CSBFS_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_sort_radix, dim3(1024), dim3(kSortThreads), 0, st, a);
+    hipLaunchKernelGGL(k_sort_radix, dim3(512), dim3(kLongThreads), 0, st, a);
     CSBFS_HIP(hipGetLastError());
     return CSBFS_OK;
 }
