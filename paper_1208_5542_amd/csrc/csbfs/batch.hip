@@ -56,6 +56,13 @@ struct BItem {
     int32_t end;
 };
 
+// A long merged row left over by the bottom-up lanes: vertex v still misses
+// some of `miss` after the row's entries before e gave `got`.
+struct BPullItem {
+    uint64_t miss, got;
+    int64_t v, e, re;
+};
+
 struct BArgs {
     uint64_t *view;  // [B][P * P * W] planes of views
     int64_t vplane;  // words per view plane
@@ -210,9 +217,8 @@ __global__ __launch_bounds__(kBThreads) void bexpand_kernel(BArgs a) {
     block_add<kBThreads / 64>(edges, a.edges);
 }
 
-__global__ __launch_bounds__(kBThreads) void bexpand_big_kernel(BArgs a) {
-    if (a.fcount && *a.fcount == 0) return;
-    if (*a.dir != CSBFS_DIR_TOP_DOWN) return;
+// Top-down long rows: the chunk-queue items of every processor.
+__device__ __forceinline__ void push_long(const BArgs &a) {
     const int lane = threadIdx.x & 63;
     const int64_t wave = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
     const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
@@ -252,6 +258,10 @@ __global__ __launch_bounds__(kBThreads) void bexpand_big_kernel(BArgs a) {
 // ---------------------------------------------------------------- pull ---
 
 constexpr int kBPullUnroll = 2;   // entries per lane step
+constexpr int kBPullWindow = 4;   // row entries a lane loads at once
+constexpr int kBPullSlots = 4;    // rows the wave reads side by side
+constexpr int kBPullLong = 2048;  // entries left from which a row goes to a whole workgroup
+constexpr int kBLongUnroll = 8;   // 64-entry steps per wave in one pass of that workgroup
 // Direction rule of batched searches (Beamer's alpha and beta over the union
 // of the roots' frontiers)
 constexpr float kBatchAlpha = 16.0f, kBatchBeta = 24.0f;
@@ -271,8 +281,22 @@ struct BPullArgs {
     const int32_t *dir;
     unsigned long long *edges;
     const unsigned long long *fcount;
+    BPullItem *queue;          // long rows, read by whole workgroups afterwards
+    int64_t queue_cap;
+    uint32_t *queue_count;
+    int32_t *status;
 };
 
+// Bottom-up level. A wave takes 64 vertices (lane = vertex): the two ids of
+// head, then kBPullRounds steps of kBPullUnroll entries per lane. The rows
+// still being read are then taken by the whole wave, 64 entries a step,
+// kBPullSlots rows side by side, and rows with kBPullLong entries or more
+// left go to a queue that whole workgroups work off (pull_long).
+//
+// Bound by chains of dependent loads (row entry, then the neighbour's mask).
+// One row at a time per wave made the longest row the level's time: scale 18,
+// 8 roots 479 us, now 71 + 53 us (pull_long); scale 24, 64 roots 16.4 ms for
+// a level that reads all 2^29 entries, now 4.9 + 4.0 ms (60 G masks/s).
 __global__ __launch_bounds__(kBThreads) void bpull_kernel(BPullArgs a) {
     if (a.fcount && *a.fcount == 0) return;
     if (*a.dir != CSBFS_DIR_BOTTOM_UP) return;
@@ -307,47 +331,168 @@ __global__ __launch_bounds__(kBThreads) void bpull_kernel(BPullArgs a) {
             e += nk;
             if (found == missing || e >= re) busy = false;
         }
-        for (int round = 0; round < kBPullRounds; ++round) {
+        // kBPullWindow entries are loaded at once (positions past the row end
+        // clamped to its last entry and masked out) and counted kBPullUnroll at
+        // a time
+        for (int round = 0; round < kBPullRounds * kBPullUnroll / kBPullWindow; ++round) {
             if (busy) {
-                // every lane reads kBPullUnroll entries, positions past the row end
-                // clamped to its last entry and masked out
-                const int32_t nk = re - e < kBPullUnroll ? (int32_t)(re - e) : kBPullUnroll;
-                uint32_t c[kBPullUnroll];
-                uint64_t m[kBPullUnroll];
+                const int32_t nw = re - e < kBPullWindow ? (int32_t)(re - e) : kBPullWindow;
+                uint32_t c[kBPullWindow];
+                uint64_t m[kBPullWindow];
 #pragma unroll
-                for (int q = 0; q < kBPullUnroll; ++q) c[q] = a.pull_col[e + (q < nk ? q : nk - 1)];
+                for (int q = 0; q < kBPullWindow; ++q) c[q] = a.pull_col[e + (q < nw ? q : nw - 1)];
 #pragma unroll
-                for (int q = 0; q < kBPullUnroll; ++q) m[q] = a.fm[c[q]];
+                for (int q = 0; q < kBPullWindow; ++q) m[q] = a.fm[c[q]];
 #pragma unroll
-                for (int q = 0; q < kBPullUnroll; ++q)
-                    if (q < nk) found |= m[q] & missing;
-                read += (unsigned long long)nk;
-                e += nk;
-                if (found == missing || e >= re) busy = false;
+                for (int h = 0; h < kBPullWindow / kBPullUnroll; ++h) {
+                    const int32_t nk = re - e < kBPullUnroll ? (int32_t)(re - e) : kBPullUnroll;
+                    if (busy) {
+#pragma unroll
+                        for (int q = 0; q < kBPullUnroll; ++q)
+                            if (q < nk) found |= m[h * kBPullUnroll + q] & missing;
+                        read += (unsigned long long)nk;
+                        e += nk;
+                        if (found == missing || e >= re) busy = false;
+                    }
+                }
             }
             if (!__ballot(busy)) break;
         }
-        // rows still being read: the whole wave takes them one at a time
         uint64_t slow = __ballot(busy);
-        while (slow) {
-            const int Ls = __ffsll((unsigned long long)slow) - 1;
-            slow &= slow - 1;
-            int64_t ee = shfl64(e, Ls);
-            const int64_t rr = shfl64(re, Ls);
-            const uint64_t miss = (uint64_t)shfl64((int64_t)missing, Ls);
-            uint64_t got = (uint64_t)shfl64((int64_t)found, Ls);
-            for (; ee < rr && got != miss; ee += 64) {
-                const int64_t pos = ee + lane;
-                const uint64_t f = pos < rr ? a.fm[a.pull_col[pos]] & miss : 0ull;
-                got |= wave_or64(f);
-                if (lane == 0) read += (unsigned long long)(rr - ee < 64 ? rr - ee : 64);
+        const bool far = busy && re - e >= kBPullLong;
+        const uint64_t deferred = __ballot(far);
+        if (deferred) {
+            slow &= ~deferred;
+            uint32_t at = 0;
+            if (lane == 0) at = atomicAdd(a.queue_count, (uint32_t)__popcll(deferred));
+            at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+            if (far) {
+                const int64_t pos = (int64_t)at + __popcll(deferred & ((1ull << lane) - 1));
+                if (pos >= a.queue_cap) {
+                    *a.status = 2;  // cannot happen: the capacity counts every such row
+                } else {
+                    a.queue[pos] = BPullItem{missing, found, v, e, re};
+                }
+                found = 0;  // pull_long writes this vertex
             }
-            if (lane == Ls) found = got;
+        }
+        // the wave's slots, all wave-uniform: row [se, sr) of lane sl
+        int64_t se[kBPullSlots], sr[kBPullSlots];
+        uint64_t smiss[kBPullSlots], sgot[kBPullSlots];
+        int sl[kBPullSlots];
+#pragma unroll
+        for (int k = 0; k < kBPullSlots; ++k) {
+            se[k] = sr[k] = 0;
+            smiss[k] = sgot[k] = 0;
+            sl[k] = -1;
+        }
+        for (;;) {
+            int live = 0;
+#pragma unroll
+            for (int k = 0; k < kBPullSlots; ++k) {
+                if (sl[k] < 0 && slow) {
+                    sl[k] = __ffsll((unsigned long long)slow) - 1;
+                    slow &= slow - 1;
+                    se[k] = (int64_t)readlane64((uint64_t)e, sl[k]);
+                    sr[k] = (int64_t)readlane64((uint64_t)re, sl[k]);
+                    smiss[k] = readlane64(missing, sl[k]);
+                    sgot[k] = readlane64(found, sl[k]);
+                }
+                live |= sl[k] >= 0;
+            }
+            if (!live) break;
+            // an empty slot reads entry 0 (there are entries) and ignores it
+            uint32_t c[kBPullSlots];
+            uint64_t f[kBPullSlots];
+#pragma unroll
+            for (int k = 0; k < kBPullSlots; ++k) {
+                const int64_t pos = se[k] + lane;
+                c[k] = a.pull_col[sl[k] < 0 ? 0 : pos < sr[k] ? pos : sr[k] - 1];
+            }
+#pragma unroll
+            for (int k = 0; k < kBPullSlots; ++k) f[k] = a.fm[c[k]] & smiss[k];  // a repeated last entry adds nothing
+#pragma unroll
+            for (int k = 0; k < kBPullSlots; ++k) {
+                if (sl[k] < 0) continue;
+                if (__ballot((f[k] & ~sgot[k]) != 0)) sgot[k] |= wave_or64(f[k]);
+                if (lane == 0) read += (unsigned long long)(sr[k] - se[k] < 64 ? sr[k] - se[k] : 64);
+                se[k] += 64;
+                if (sgot[k] == smiss[k] || se[k] >= sr[k]) {
+                    if (lane == sl[k]) found = sgot[k];
+                    sl[k] = -1;
+                }
+            }
         }
         if (found) a.vn[2 * v + 1] = found;  // this lane's vertex: no other writer
     }
     for (int d = 32; d > 0; d >>= 1) read += (unsigned long long)shfl64((int64_t)read, lane ^ d);
     block_add<kBThreads / 64>(read, a.edges);
+}
+
+// Bottom-up long rows: a workgroup takes one row, kBLongUnroll * 64 entries
+// per wave and pass, until every missing root is found or the row ends. The
+// entries read are counted to the 64-entry step that completes the mask.
+__device__ __forceinline__ void pull_long(const BPullArgs &a) {
+    constexpr int kWaves = kBThreads / 64;
+    constexpr int kStep = 64 * kBLongUnroll, kPass = kWaves * kStep;
+    __shared__ uint64_t part[2][kWaves];
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    const int64_t count = (int64_t)*a.queue_count < a.queue_cap ? (int64_t)*a.queue_count : a.queue_cap;
+    unsigned long long read = 0;
+    int par = 0;
+    for (int64_t it = blockIdx.x; it < count; it += gridDim.x) {
+        const BPullItem x = a.queue[it];
+        uint64_t got = x.got;
+        for (int64_t e = x.e; e < x.re && got != x.miss; e += kPass) {
+            const int64_t e0 = e + (int64_t)wid * kStep;
+            uint32_t c[kBLongUnroll];
+            uint64_t f[kBLongUnroll];
+#pragma unroll
+            for (int k = 0; k < kBLongUnroll; ++k) {
+                const int64_t pos = e0 + 64 * k + lane;
+                c[k] = a.pull_col[pos < x.re ? pos : x.re - 1];
+            }
+            uint64_t any = 0;
+#pragma unroll
+            for (int k = 0; k < kBLongUnroll; ++k) {
+                f[k] = e0 + 64 * k + lane < x.re ? a.fm[c[k]] & x.miss : 0ull;
+                any |= f[k];
+            }
+            any = __ballot((any & ~got) != 0) ? wave_or64(any) : 0ull;
+            if (lane == 0) part[par][wid] = any;
+            __syncthreads();  // one barrier a pass: the parts alternate
+            uint64_t before = got;
+            for (int w = 0; w < wid; ++w) before |= part[par][w];
+            uint64_t all = before;
+            for (int w = wid; w < kWaves; ++w) all |= part[par][w];
+            if (all == x.miss && before != x.miss && (before | any) == x.miss) {
+                // this wave's steps complete the mask: which one
+                for (int k = 0; k < kBLongUnroll && before != x.miss; ++k) {
+                    before |= wave_or64(f[k]);
+                    if (before == x.miss) {
+                        const int64_t end = e0 + 64 * (k + 1);
+                        read += (unsigned long long)((end < x.re ? end : x.re) - e);
+                    }
+                }
+            } else if (all != x.miss && wid == 0) {
+                read += (unsigned long long)(x.re - e < kPass ? x.re - e : kPass);
+            }
+            got = all;
+            par ^= 1;
+        }
+        if (threadIdx.x == 0 && got) a.vn[2 * x.v + 1] = got;
+    }
+    block_add<kWaves>(read, a.edges);
+}
+
+// The level's long rows, in the direction it was expanded in.
+__global__ __launch_bounds__(kBThreads) void blong_kernel(BArgs a, BPullArgs pa) {
+    if (a.fcount && *a.fcount == 0) return;
+    const int32_t d = *a.dir;
+    if (d == CSBFS_DIR_TOP_DOWN)
+        push_long(a);
+    else if (d == CSBFS_DIR_BOTTOM_UP)
+        pull_long(pa);
 }
 
 // Direction state of a batched search, carried from level to level.
@@ -390,7 +535,7 @@ struct BUpdateArgs {
     int64_t n;
     unsigned long long *root_count;  // [B]
     unsigned long long *total;       // [1]
-    uint32_t *queue_count;           // [P], cleared for the next level
+    uint32_t *queue_count;           // [P + 1], cleared for the next level
     int32_t P;
     const unsigned long long *fcount;  // as in BArgs: 0 visits nothing
     uint64_t *fm;                      // [n]: frontier mask of every vertex (written for all)
@@ -408,7 +553,7 @@ __global__ __launch_bounds__(kBThreads) void bupdate_kernel(BUpdateArgs a) {
     if (threadIdx.x < kMaxRoots) cnt[threadIdx.x] = 0;
     if (threadIdx.x < 3) dsum[threadIdx.x] = 0;
     if (blockIdx.x == 0)
-        for (int q = threadIdx.x; q < a.P; q += blockDim.x) a.queue_count[q] = 0;
+        for (int q = threadIdx.x; q <= a.P; q += blockDim.x) a.queue_count[q] = 0;
     __syncthreads();
     const int64_t words = a.n / 64;
     const int64_t ntiles = (words + kBTile - 1) / kBTile;
@@ -552,7 +697,9 @@ struct csbfs_batch_engine {
     int64_t *chunk_groups = nullptr;
     BItem *queue = nullptr;
     int64_t *qoff = nullptr;
-    uint32_t *qcount = nullptr;
+    uint32_t *qcount = nullptr;       // [P] top-down chunk queues, then the bottom-up long rows
+    BPullItem *pqueue = nullptr;
+    int64_t pqueue_cap = 0;
     int64_t *roots_dev = nullptr;
     int32_t *status = nullptr;
     void *counters_mem = nullptr;
@@ -594,15 +741,18 @@ namespace {
 // the one block they are carved from (each buffer 256-byte aligned).
 struct BatchSizes {
     int64_t vis, nx, f, view, arena, look, ticket, chunk, queue, qoff, qcount, roots, status, counters;
-    int64_t fm, dstate, dirs;
+    int64_t fm, dstate, dirs, pqueue;
     int64_t total() const {
         int64_t t = 0;
         for (int64_t b : {vis, f, view, arena, look + ticket, chunk, queue, qoff, qcount, roots, status, counters, fm,
-                          dstate, dirs})
+                          dstate, dirs, pqueue})
             t += align_up(b > 0 ? b : 1);
         return t;
     }
 };
+
+// Rows with kBPullLong entries or more: each is queued at most once a level.
+int64_t pull_long_rows(int64_t nnz) { return nnz / kBPullLong + 1; }
 
 BatchSizes batch_sizes(const csbfs_graph *g, int64_t B, int64_t L, uint32_t flags) {
     const int64_t P = g->P, n = g->n;
@@ -621,7 +771,8 @@ BatchSizes batch_sizes(const csbfs_graph *g, int64_t B, int64_t L, uint32_t flag
     z.chunk = 8 * Smax * dec_chunks(g->R);
     z.queue = (int64_t)sizeof(BItem) * (items > 0 ? items : 1);
     z.qoff = 8 * (P + 1);
-    z.qcount = 4 * P;
+    z.qcount = 4 * (P + 1);
+    z.pqueue = (int64_t)sizeof(BPullItem) * pull_long_rows(g->nnz);
     z.roots = 8 * B;
     z.status = 4;
     z.counters = 8 * slots * (1 + B + 1 + Smax + B * P) + 8 * slots * Smax;
@@ -714,6 +865,8 @@ int batch_engine_make(const csbfs_graph *g, int32_t max_roots, int32_t max_level
     e->fm = (uint64_t *)carve(z.fm);
     e->dstate = (BDirState *)carve(z.dstate);
     e->dirs = (int32_t *)carve(z.dirs);
+    e->pqueue = (BPullItem *)carve(z.pqueue);
+    e->pqueue_cap = pull_long_rows(g->nnz);
     e->counters_mem = carve(z.counters);
     e->counters_bytes = (size_t)z.counters;
     e->look_bytes = (size_t)(z.look + z.ticket);
@@ -787,7 +940,7 @@ extern "C" int csbfs_batch_bfs(csbfs_batch_engine *e, const int64_t *roots, int3
     // a0: seed every root
     CSBFS_HIP(hipMemsetAsync(e->counters_mem, 0, e->counters_bytes, st));
     CSBFS_HIP(hipMemsetAsync(e->status, 0, sizeof(int32_t), st));
-    CSBFS_HIP(hipMemsetAsync(e->qcount, 0, sizeof(uint32_t) * P, st));
+    CSBFS_HIP(hipMemsetAsync(e->qcount, 0, sizeof(uint32_t) * (P + 1), st));
     // the encoder's tickets count on over the batch's levels: start them at zero
     CSBFS_HIP(hipMemsetAsync(e->look, 0, e->look_bytes, st));
     CSBFS_HIP(hipMemcpyAsync(e->roots_dev, roots, sizeof(int64_t) * B, hipMemcpyHostToDevice, st));
@@ -832,6 +985,10 @@ extern "C" int csbfs_batch_bfs(csbfs_batch_engine *e, const int64_t *roots, int3
     pa.n = n;
     pa.B = (int32_t)B;
     pa.dir = &e->dstate->cur;
+    pa.queue = e->pqueue;
+    pa.queue_cap = e->pqueue_cap;
+    pa.queue_count = e->qcount + P;
+    pa.status = e->status;
 
     WahBatch wb{};
     wb.bits_base = e->f;
@@ -887,15 +1044,15 @@ extern "C" int csbfs_batch_bfs(csbfs_batch_engine *e, const int64_t *roots, int3
         ea.fcount = fc;
         hipLaunchKernelGGL(bexpand_kernel, dim3(grid), dim3(kBThreads), 0, st, ea);
         CSBFS_HIP(hipGetLastError());
-        // long rows: 1024 workgroups beat 512, 2048 and 4096 (a sweep, within 2%)
-        hipLaunchKernelGGL(bexpand_big_kernel, dim3(1024), dim3(kBThreads), 0, st, ea);
-        CSBFS_HIP(hipGetLastError());
         // the bottom-up evaluation (returns at once on top-down levels); past
         // the kept counters every root counts as active
         pa.rootc = j < e->L ? e->rootc + sj * Bm : nullptr;
         pa.edges = e->edges + sj;
         pa.fcount = fc;
         hipLaunchKernelGGL(bpull_kernel, dim3(grid), dim3(kBThreads), 0, st, pa);
+        CSBFS_HIP(hipGetLastError());
+        // long rows: 1024 workgroups beat 512, 2048 and 4096 (a sweep, within 2%)
+        hipLaunchKernelGGL(blong_kernel, dim3(1024), dim3(kBThreads), 0, st, ea, pa);
         CSBFS_HIP(hipGetLastError());
         if (ev) CSBFS_HIP(hipEventRecord(ev[1], st));
         BUpdateArgs ua{e->vn, e->f, level, (int32_t)(j + 1), (int32_t)B, n,

@@ -5,14 +5,43 @@
 
 namespace csbfs {
 
-__device__ __forceinline__ int wave_incl_scan_i32(int v) {
-    const int lane = threadIdx.x & 63;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        int t = __shfl_up(v, d, 64);
-        if (lane >= d) v += t;
-    }
-    return v;
+// v of the lane that kCtrl names, 0 where there is none (lanes of the rows
+// outside kRows keep 0 too). DPP moves stay in the vector pipeline: a scan or
+// reduction step costs a few cycles, where a shuffle through the LDS crossbar
+// costs a round trip of about 60.
+template <int kCtrl, int kRows = 0xf>
+__device__ __forceinline__ uint32_t dpp0(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kCtrl, kRows, 0xf, false);
+}
+template <int kCtrl, int kRows = 0xf>
+__device__ __forceinline__ uint64_t dpp0_64(uint64_t v) {
+    return ((uint64_t)dpp0<kCtrl, kRows>((uint32_t)(v >> 32)) << 32) | dpp0<kCtrl, kRows>((uint32_t)v);
+}
+// DPP controls: lane - d within its row of 16; the last lane of the row (of
+// the lower 32 lanes) before, into rows 1 and 3 (rows 2 and 3)
+constexpr int kDppShr1 = 0x111, kDppShr2 = 0x112, kDppShr4 = 0x114, kDppShr8 = 0x118;
+constexpr int kDppBcast15 = 0x142, kDppBcast31 = 0x143;
+
+// Inclusive scans over the wave; every lane must be active.
+__device__ __forceinline__ int wave_incl_scan_i32(int x) {
+    uint32_t v = (uint32_t)x;
+    v += dpp0<kDppShr1>(v);
+    v += dpp0<kDppShr2>(v);
+    v += dpp0<kDppShr4>(v);
+    v += dpp0<kDppShr8>(v);
+    v += dpp0<kDppBcast15, 0xa>(v);
+    v += dpp0<kDppBcast31, 0xc>(v);
+    return (int)v;
+}
+__device__ __forceinline__ long long wave_incl_scan_i64(long long x) {
+    uint64_t v = (uint64_t)x;
+    v += dpp0_64<kDppShr1>(v);
+    v += dpp0_64<kDppShr2>(v);
+    v += dpp0_64<kDppShr4>(v);
+    v += dpp0_64<kDppShr8>(v);
+    v += dpp0_64<kDppBcast15, 0xa>(v);
+    v += dpp0_64<kDppBcast31, 0xc>(v);
+    return (long long)v;
 }
 
 // Owner lane of slot x: the largest lane L whose exclusive prefix excl[L] is
@@ -79,10 +108,15 @@ __device__ __forceinline__ uint64_t readlane64(uint64_t v, int src) {
     return ((uint64_t)hi << 32) | lo;
 }
 
+// OR over the wave, in every lane; every lane must be active.
 __device__ __forceinline__ uint64_t wave_or64(uint64_t v) {
-#pragma unroll
-    for (int d = 32; d > 0; d >>= 1) v |= (uint64_t)shfl64((int64_t)v, (threadIdx.x & 63) ^ d);
-    return v;
+    v |= dpp0_64<kDppShr1>(v);
+    v |= dpp0_64<kDppShr2>(v);
+    v |= dpp0_64<kDppShr4>(v);
+    v |= dpp0_64<kDppShr8>(v);
+    v |= dpp0_64<kDppBcast15, 0xa>(v);
+    v |= dpp0_64<kDppBcast31, 0xc>(v);
+    return readlane64(v, 63);
 }
 
 // Orders a wave's LDS stores before its later LDS loads by other lanes (and

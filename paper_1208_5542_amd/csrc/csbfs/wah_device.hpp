@@ -34,26 +34,6 @@ namespace {
 // LDS words that stage a segment of seg groups and the group before it
 constexpr int enc_lds_words(int seg) { return ((seg + 2) * kGroupBits) / 64 + 4; }
 
-__device__ __forceinline__ int wave_incl_scan(int v) {
-    const int lane = threadIdx.x & (kWave - 1);
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-        int t = __shfl_up(v, d, kWave);
-        if (lane >= d) v += t;
-    }
-    return v;
-}
-
-__device__ __forceinline__ long long wave_incl_scan64(long long v) {
-    const int lane = threadIdx.x & (kWave - 1);
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-        long long t = __shfl_up(v, d, kWave);
-        if (lane >= d) v += t;
-    }
-    return v;
-}
-
 // Exclusive scan over the block (blockDim.x a multiple of 64, at most 1024);
 // returns the exclusive prefix and writes the block total to *total.
 __device__ int block_excl_scan(int v, int *total) {
@@ -61,12 +41,12 @@ __device__ int block_excl_scan(int v, int *total) {
     const int lane = threadIdx.x & (kWave - 1);
     const int wid = threadIdx.x / kWave;
     const int nw = blockDim.x / kWave;
-    int incl = wave_incl_scan(v);
+    int incl = wave_incl_scan_i32(v);
     if (lane == kWave - 1) wsum[wid] = incl;
     __syncthreads();
     if (wid == 0) {
         int s = lane < nw ? wsum[lane] : 0;
-        s = wave_incl_scan(s);
+        s = wave_incl_scan_i32(s);
         if (lane < nw) wsum[lane] = s;
     }
     __syncthreads();
@@ -81,12 +61,12 @@ __device__ long long block_excl_scan64(long long v, long long *total) {
     const int lane = threadIdx.x & (kWave - 1);
     const int wid = threadIdx.x / kWave;
     const int nw = blockDim.x / kWave;
-    long long incl = wave_incl_scan64(v);
+    long long incl = wave_incl_scan_i64(v);
     if (lane == kWave - 1) wsum64[wid] = incl;
     __syncthreads();
     if (wid == 0) {
         long long s = lane < nw ? wsum64[lane] : 0;
-        s = wave_incl_scan64(s);
+        s = wave_incl_scan_i64(s);
         if (lane < nw) wsum64[lane] = s;
     }
     __syncthreads();
