@@ -37,7 +37,7 @@
 #include <memory>
 #include <vector>
 
-#include "device.hpp"
+#include "wah_device.hpp"
 #include "graph.hpp"
 
 namespace csbfs {
@@ -507,23 +507,48 @@ struct BDirState {
 // update): top-down turns bottom-up when the frontier's entries times alpha
 // exceed the entries of vertices some root has not reached and the frontier
 // did not shrink; bottom-up turns top-down when the frontier is below
-// n / beta and shrinking. The sums are cleared for the next update.
-__global__ void bdir_kernel(BDirState *st, int32_t *rec, int64_t n, float alpha, float beta) {
-    BDirState s = *st;
+// n / beta and shrinking. The sums are cleared for the next update, and the
+// level's frontier size is posted for the host.
+struct BDirArgs {
+    BDirState *st;
+    int32_t *rec;  // nullable
+    int64_t n;
+    float alpha, beta;
+    const unsigned long long *total;  // frontier size of the level
+    unsigned long long *host;         // pinned word: level tag << kPostBits | size
+    int64_t level;
+};
+constexpr int kPostBits = 40;  // sizes are at most 64 n < 2^38; the tag is the level's low 24 bits
+
+__device__ void bdir_choose(const BDirArgs &a) {
+    BDirState s = *a.st;
     const unsigned long long nf = s.sums[0], mf = s.sums[1], mu = s.sums[2];
     int32_t next = s.cur;
     if (s.force >= 0) {
         next = s.force;
     } else if (s.cur == CSBFS_DIR_TOP_DOWN) {
-        if ((double)mf * alpha > (double)mu && nf >= s.prev) next = CSBFS_DIR_BOTTOM_UP;
-    } else if ((double)nf * beta < (double)n && nf < s.prev) {
+        if ((double)mf * a.alpha > (double)mu && nf >= s.prev) next = CSBFS_DIR_BOTTOM_UP;
+    } else if ((double)nf * a.beta < (double)a.n && nf < s.prev) {
         next = CSBFS_DIR_TOP_DOWN;
     }
     s.prev = nf;
     s.cur = next;
     s.sums[0] = s.sums[1] = s.sums[2] = 0;
-    *st = s;
-    if (rec) *rec = next;
+    *a.st = s;
+    if (a.rec) *a.rec = next;
+    __hip_atomic_store(a.host, ((unsigned long long)a.level << kPostBits) | *a.total, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// Sieve + compress of a level's frontier planes; the first workgroup also
+// chooses the direction of the expansion that follows (nothing else of this
+// launch reads the direction state) and posts the level's size. A launch of
+// one thread for that and a copy of the size cost two of eight commands per
+// level.
+__global__ __launch_bounds__(kEncThreads) void bencode_kernel(WahBatch b, BDirArgs d) {
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) bdir_choose(d);
+    PlainWords h;
+    encode_segment<kEncGpt>(b, h, blockIdx.y, blockIdx.x == 0);
 }
 
 struct BUpdateArgs {
@@ -636,23 +661,31 @@ struct BSeedArgs {
     int32_t *level;
     int64_t level_words;  // n_roots * n
     int64_t n;
+    uint32_t *zero;       // counters, look-back words and tickets, queue counts, status
+    int64_t zero_words;
+};
+
+struct BRoots {
+    int64_t v[kMaxRoots];
 };
 
 __global__ void bseed_fill_kernel(BSeedArgs a) {
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    const int64_t top = a.view_words > a.level_words ? a.view_words : a.level_words;
+    int64_t top = a.view_words > a.level_words ? a.view_words : a.level_words;
+    top = top > a.zero_words ? top : a.zero_words;
     for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < top; k += stride) {
         if (k < a.n) {
             reinterpret_cast<ulonglong2 *>(a.vn)[k] = make_ulonglong2(0ull, 0ull);
             a.fm[k] = 0;
         }
+        if (k < a.zero_words) a.zero[k] = 0;
         if (k < a.view_words) a.view[k] = 0;
         if (k < a.level_words) a.level[k] = -1;
     }
 }
 
 // f(s) <- s for every root: known to every processor without a message.
-__global__ void bseed_root_kernel(BSeedArgs a, const int64_t *roots, int32_t B, int64_t R, int64_t W,
+__global__ void bseed_root_kernel(BSeedArgs a, BRoots roots, int32_t B, int64_t R, int64_t W,
                                   int32_t P, int64_t vplane, unsigned long long *root_count0,
                                   unsigned long long *total0, BDirState *ds, int32_t dir0, int32_t force,
                                   int32_t *rec0) {
@@ -666,7 +699,7 @@ __global__ void bseed_root_kernel(BSeedArgs a, const int64_t *roots, int32_t B, 
         if (rec0) *rec0 = dir0;
     }
     if (r >= B) return;
-    const int64_t s = roots[r];
+    const int64_t s = roots.v[r];
     const int64_t own = s / R, sl = s - own * R;
     atomicOr((unsigned long long *)(a.vn + 2 * s), 1ull << r);
     atomicOr((unsigned long long *)(a.fm + s), 1ull << r);
@@ -690,28 +723,31 @@ struct csbfs_batch_engine {
     uint64_t *vn = nullptr, *f = nullptr, *view = nullptr, *arena = nullptr;
     uint64_t *fm = nullptr;           // [n] frontier mask of every vertex (bottom-up levels)
     BDirState *dstate = nullptr;
-    int32_t *dirs = nullptr;          // [L + 1] direction used to expand each level
     unsigned long long *look = nullptr;  // encoder look-back words [Smax * nseg]
     uint32_t *enc_ticket = nullptr;      // [kTicketStride * Smax], after look
-    size_t look_bytes = 0;
     int64_t *chunk_groups = nullptr;
     BItem *queue = nullptr;
     int64_t *qoff = nullptr;
     uint32_t *qcount = nullptr;       // [P] top-down chunk queues, then the bottom-up long rows
     BPullItem *pqueue = nullptr;
     int64_t pqueue_cap = 0;
-    int64_t *roots_dev = nullptr;
     int32_t *status = nullptr;
-    void *counters_mem = nullptr;
-    size_t counters_bytes = 0;
-    unsigned long long *ctl = nullptr;    // [L+1] total frontier
-    unsigned long long *rootc = nullptr;  // [L+1][Bmax]
-    unsigned long long *edges = nullptr;  // [L+1]
-    unsigned long long *sbits = nullptr;  // [L+1][Smax]
-    unsigned long long *uwords = nullptr; // [L+1][Bmax * P]
-    int64_t *words = nullptr;             // [L+1][Smax]
-    unsigned long long *host_ctl = nullptr;  // pinned [2]
-    hipEvent_t count_ev[2] = {nullptr, nullptr};
+    // one block that a batch starts from zero: status and queue counts, a
+    // record of `stride` words per level (slot L for levels past max_levels),
+    // the look-back words and tickets. A search's status and statistics are
+    // one copy from its start.
+    uint32_t *zero_mem = nullptr;
+    int64_t zero_words = 0, hdr = 0, stride = 0;
+    unsigned long long *recs = nullptr;
+    unsigned long long *ctl(int64_t k) const { return recs + k * stride; }  // total frontier
+    unsigned long long *edges(int64_t k) const { return ctl(k) + 1; }
+    int32_t *dir(int64_t k) const { return (int32_t *)(ctl(k) + 2); }  // direction used to expand the level
+    unsigned long long *rootc(int64_t k) const { return ctl(k) + 3; }                 // [Bmax]
+    unsigned long long *uwords(int64_t k) const { return rootc(k) + Bmax; }           // [Bmax * P]
+    unsigned long long *sbits(int64_t k) const { return uwords(k) + Bmax * g->P; }    // [Smax]
+    int64_t *words(int64_t k) const { return (int64_t *)(sbits(k) + Smax); }          // [Smax]
+    unsigned long long *host_ctl = nullptr;      // pinned [2]
+    unsigned long long *host_ctl_dev = nullptr;  // its device address
     std::vector<hipEvent_t> events;
     void *mem = nullptr;     // every device buffer, carved from one block
     bool owns_mem = false;   // hipMalloc'd here (else the caller's, e.g. the server's pool)
@@ -726,8 +762,6 @@ namespace {
 void bengine_release(csbfs_batch_engine *e) {
     if (e->owns_mem && e->mem) (void)hipFree(e->mem);
     if (e->owns_host && e->host_ctl) (void)hipHostFree(e->host_ctl);
-    for (hipEvent_t ev : e->count_ev)
-        if (ev) (void)hipEventDestroy(ev);
     for (hipEvent_t ev : e->events)
         if (ev) (void)hipEventDestroy(ev);
     delete e;
@@ -740,12 +774,11 @@ namespace {
 // Device bytes of every buffer of a batch engine; total() is the size of
 // the one block they are carved from (each buffer 256-byte aligned).
 struct BatchSizes {
-    int64_t vis, nx, f, view, arena, look, ticket, chunk, queue, qoff, qcount, roots, status, counters;
-    int64_t fm, dstate, dirs, pqueue;
+    int64_t vis, f, view, arena, chunk, queue, qoff, zero, fm, dstate, pqueue;
+    int64_t hdr, stride;  // words before the first record, words per record
     int64_t total() const {
         int64_t t = 0;
-        for (int64_t b : {vis, f, view, arena, look + ticket, chunk, queue, qoff, qcount, roots, status, counters, fm,
-                          dstate, dirs, pqueue})
+        for (int64_t b : {vis, f, view, arena, chunk, queue, qoff, zero, fm, dstate, pqueue})
             t += align_up(b > 0 ? b : 1);
         return t;
     }
@@ -762,23 +795,18 @@ BatchSizes batch_sizes(const csbfs_graph *g, int64_t B, int64_t L, uint32_t flag
     for (int64_t r = 0; r < P; ++r) items += g->big_items[r];
     BatchSizes z{};
     z.vis = 16 * n;
-    z.nx = 0;
     z.f = 8 * B * (n / 64);
     z.view = 8 * B * P * (n / 64);
     z.arena = 8 * Smax * wah_cap(g->R) * arena_slots;
-    z.look = 8 * Smax * enc_segments(g->R);
-    z.ticket = 4 * kTicketStride * Smax;
     z.chunk = 8 * Smax * dec_chunks(g->R);
     z.queue = (int64_t)sizeof(BItem) * (items > 0 ? items : 1);
     z.qoff = 8 * (P + 1);
-    z.qcount = 4 * (P + 1);
     z.pqueue = (int64_t)sizeof(BPullItem) * pull_long_rows(g->nnz);
-    z.roots = 8 * B;
-    z.status = 4;
-    z.counters = 8 * slots * (1 + B + 1 + Smax + B * P) + 8 * slots * Smax;
+    z.hdr = 1 + (P + 2) / 2;  // status, then P + 1 queue counts
+    z.stride = 3 + B + B * P + 2 * Smax;
+    z.zero = 8 * (z.hdr + slots * z.stride) + 8 * Smax * enc_segments(g->R) + 4 * kTicketStride * Smax;
     z.fm = 8 * n;
     z.dstate = (int64_t)sizeof(BDirState);
-    z.dirs = 4 * slots;
     return z;
 }
 
@@ -822,7 +850,6 @@ int batch_engine_make(const csbfs_graph *g, int32_t max_roots, int32_t max_level
     e->nseg = enc_segments(g->R);
     e->nchunk = dec_chunks(g->R);
     e->Smax = B * P * P;
-    const int64_t slots = (int64_t)max_levels + 1;
     std::vector<int64_t> qoff(P + 1, 0);
     for (int64_t r = 0; r < P; ++r) qoff[r + 1] = qoff[r] + g->big_items[r];
     const BatchSizes z = batch_sizes(g, B, max_levels, flags);
@@ -853,42 +880,29 @@ int batch_engine_make(const csbfs_graph *g, int32_t max_roots, int32_t max_level
     e->f = (uint64_t *)carve(z.f);
     e->view = (uint64_t *)carve(z.view);
     e->arena = (uint64_t *)carve(z.arena);
-    // encoder look-back words, then its tickets: zero before the first encode
-    e->look = (unsigned long long *)carve(z.look + z.ticket);
-    e->enc_ticket = reinterpret_cast<uint32_t *>(e->look + e->Smax * e->nseg);
     e->chunk_groups = (int64_t *)carve(z.chunk);
     e->queue = (BItem *)carve(z.queue);
     e->qoff = (int64_t *)carve(z.qoff);
-    e->qcount = (uint32_t *)carve(z.qcount);
-    e->roots_dev = (int64_t *)carve(z.roots);
-    e->status = (int32_t *)carve(z.status);
+    e->zero_mem = (uint32_t *)carve(z.zero);
+    e->zero_words = z.zero / 4;
+    e->hdr = z.hdr;
+    e->stride = z.stride;
+    e->status = (int32_t *)e->zero_mem;
+    e->qcount = e->zero_mem + 2;
+    e->recs = (unsigned long long *)e->zero_mem + z.hdr;
+    e->look = e->recs + ((int64_t)max_levels + 1) * z.stride;
+    e->enc_ticket = reinterpret_cast<uint32_t *>(e->look + e->Smax * e->nseg);
     e->fm = (uint64_t *)carve(z.fm);
     e->dstate = (BDirState *)carve(z.dstate);
-    e->dirs = (int32_t *)carve(z.dirs);
     e->pqueue = (BPullItem *)carve(z.pqueue);
     e->pqueue_cap = pull_long_rows(g->nnz);
-    e->counters_mem = carve(z.counters);
-    e->counters_bytes = (size_t)z.counters;
-    e->look_bytes = (size_t)(z.look + z.ticket);
-    unsigned long long *c = (unsigned long long *)e->counters_mem;
-    e->ctl = c;
-    c += slots;
-    e->rootc = c;
-    c += slots * B;
-    e->edges = c;
-    c += slots;
-    e->sbits = c;
-    c += slots * e->Smax;
-    e->uwords = c;
-    c += slots * B * P;
-    e->words = (int64_t *)c;
-    hipError_t herr = hipMemsetAsync(e->look, 0, e->look_bytes, st);
+    void *hdev = nullptr;
+    hipError_t herr = hipHostGetDevicePointer(&hdev, e->host_ctl, 0);
+    e->host_ctl_dev = (unsigned long long *)hdev;
     if (herr == hipSuccess)
         herr = hipMemcpyAsync(e->qoff, qoff.data(), sizeof(int64_t) * (P + 1), hipMemcpyHostToDevice, st);
     if (herr == hipSuccess) herr = hipMemsetAsync(e->view, 0, sizeof(uint64_t) * B * P * (n / 64), st);
     if (herr == hipSuccess) herr = hipStreamSynchronize(st);  // qoff is read from host memory
-    for (auto &ev : e->count_ev)
-        if (herr == hipSuccess) herr = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
     if (herr == hipSuccess && (flags & CSBFS_FLAG_TIMING)) {
         e->events.assign((size_t)max_levels * kBEvPerLevel, nullptr);
         for (auto &ev : e->events)  // timestamps only: no system-scope fence at each record
@@ -938,23 +952,22 @@ extern "C" int csbfs_batch_bfs(csbfs_batch_engine *e, const int64_t *roots, int3
     const bool keep = (e->flags & CSBFS_FLAG_KEEP_STREAMS) != 0;
 
     // a0: seed every root
-    CSBFS_HIP(hipMemsetAsync(e->counters_mem, 0, e->counters_bytes, st));
-    CSBFS_HIP(hipMemsetAsync(e->status, 0, sizeof(int32_t), st));
-    CSBFS_HIP(hipMemsetAsync(e->qcount, 0, sizeof(uint32_t) * (P + 1), st));
-    // the encoder's tickets count on over the batch's levels: start them at zero
-    CSBFS_HIP(hipMemsetAsync(e->look, 0, e->look_bytes, st));
-    CSBFS_HIP(hipMemcpyAsync(e->roots_dev, roots, sizeof(int64_t) * B, hipMemcpyHostToDevice, st));
-    BSeedArgs sa{e->vn, e->fm, e->view, B * vplane, level, B * n, n};
+    // (its fill also clears the counters and the encoder's tickets, which count
+    // on over the batch's levels)
+    BSeedArgs sa{e->vn, e->fm, e->view, B * vplane, level, B * n, n, e->zero_mem, e->zero_words};
+    BRoots rt{};
+    std::copy(roots, roots + B, rt.v);
+    e->host_ctl[0] = e->host_ctl[1] = 0;  // level tags start at 1
     // evaluation of each level: top-down, bottom-up, or chosen on the device
     const int32_t force = (e->flags & CSBFS_FLAG_SPARSE_ONLY)      ? CSBFS_DIR_TOP_DOWN
                           : (e->flags & CSBFS_FLAG_BOTTOM_UP_ONLY) ? CSBFS_DIR_BOTTOM_UP
                                                                    : -1;
     const int32_t dir0 = force == CSBFS_DIR_BOTTOM_UP ? CSBFS_DIR_BOTTOM_UP : CSBFS_DIR_TOP_DOWN;
-    const int64_t fill = B * n > B * vplane ? B * n : B * vplane;
+    const int64_t fill = std::max(std::max(B * n, B * vplane), e->zero_words);
     hipLaunchKernelGGL(bseed_fill_kernel, dim3(grid_for(fill, 256, 16384)), dim3(256), 0, st, sa);
     CSBFS_HIP(hipGetLastError());
-    hipLaunchKernelGGL(bseed_root_kernel, dim3(1), dim3(64), 0, st, sa, (const int64_t *)e->roots_dev,
-                       (int32_t)B, R, W, (int32_t)P, vplane, e->rootc, e->ctl, e->dstate, dir0, force, e->dirs);
+    hipLaunchKernelGGL(bseed_root_kernel, dim3(1), dim3(64), 0, st, sa, rt, (int32_t)B, R, W, (int32_t)P,
+                       vplane, e->rootc(0), e->ctl(0), e->dstate, dir0, force, e->dir(0));
     CSBFS_HIP(hipGetLastError());
 
     BArgs ea{};
@@ -1012,42 +1025,39 @@ extern "C" int csbfs_batch_bfs(csbfs_batch_engine *e, const int64_t *roots, int3
     auto slot = [&](int64_t k) { return k < e->L ? k : (int64_t)e->L; };
     auto enqueue_iter = [&](int64_t j) -> int {
         const int64_t sj = slot(j), sn = slot(j + 1);
-        if (j + 1 >= e->L) {
-            const int64_t Lz = e->L;
-            CSBFS_HIP(hipMemsetAsync(e->ctl + Lz, 0, sizeof(unsigned long long), st));
-            CSBFS_HIP(hipMemsetAsync(e->rootc + Lz * Bm, 0, sizeof(unsigned long long) * Bm, st));
-            CSBFS_HIP(hipMemsetAsync(e->edges + Lz, 0, sizeof(unsigned long long), st));
-            CSBFS_HIP(hipMemsetAsync(e->sbits + Lz * e->Smax, 0, sizeof(unsigned long long) * e->Smax, st));
-            CSBFS_HIP(hipMemsetAsync(e->uwords + Lz * Bm * P, 0, sizeof(unsigned long long) * Bm * P, st));
-        }
         hipEvent_t *evp = (timing && j >= 1 && j - 1 < e->L) ? &e->events[(size_t)(j - 1) * kBEvPerLevel] : nullptr;
         hipEvent_t *ev = (timing && j < e->L) ? &e->events[(size_t)j * kBEvPerLevel] : nullptr;
         if (j >= 1) {
             wb.out_base = e->arena + (keep ? sj : 0) * e->Smax * e->cap;
-            wb.n_words = e->words + sj * e->Smax;
-            wb.stat_sieved_bits = e->sbits + sj * e->Smax;
-            wb.stat_unsieved_words = e->uwords + sj * Bm * P;
+            wb.n_words = e->words(sj);
+            wb.stat_sieved_bits = e->sbits(sj);
+            wb.stat_unsieved_words = e->uwords(sj);
             // roots whose level-j frontier is empty send nothing (the counter
             // slot past max_levels is reset before this encode: no skipping)
-            wb.plane_count = j < e->L ? e->rootc + sj * Bm : nullptr;
-            int r2 = launch_wah_encode(wb, st);
-            if (r2) return r2;
+            wb.plane_count = j < e->L ? e->rootc(sj) : nullptr;
+            const BDirArgs bd{e->dstate, j < e->L ? e->dir(j) : nullptr, n, kBatchAlpha, kBatchBeta, e->ctl(sj),
+                              e->host_ctl_dev + (j & 1), j};
+            hipLaunchKernelGGL(bencode_kernel, dim3((unsigned)wb.nseg, (unsigned)batch_streams(wb)), dim3(kEncThreads), 0,
+                               st, wb, bd);
+            CSBFS_HIP(hipGetLastError());
             if (evp) CSBFS_HIP(hipEventRecord(evp[3], st));
-            r2 = launch_wah_decode(wb, st);
+            const int r2 = launch_wah_decode(wb, st);
             if (r2) return r2;
             if (evp) CSBFS_HIP(hipEventRecord(evp[4], st));
         }
+        // the slot past max_levels, once this level's size has been posted
+        if (j + 1 >= e->L) CSBFS_HIP(hipMemsetAsync(e->ctl(e->L), 0, 8 * e->stride, st));
         if (ev) CSBFS_HIP(hipEventRecord(ev[0], st));
         // the iteration after the last level (one of look-ahead) does nothing
-        const unsigned long long *fc = j < e->L ? e->ctl + sj : nullptr;
-        ea.edges = e->edges + sj;
+        const unsigned long long *fc = j < e->L ? e->ctl(sj) : nullptr;
+        ea.edges = e->edges(sj);
         ea.fcount = fc;
         hipLaunchKernelGGL(bexpand_kernel, dim3(grid), dim3(kBThreads), 0, st, ea);
         CSBFS_HIP(hipGetLastError());
         // the bottom-up evaluation (returns at once on top-down levels); past
         // the kept counters every root counts as active
-        pa.rootc = j < e->L ? e->rootc + sj * Bm : nullptr;
-        pa.edges = e->edges + sj;
+        pa.rootc = j < e->L ? e->rootc(sj) : nullptr;
+        pa.edges = e->edges(sj);
         pa.fcount = fc;
         hipLaunchKernelGGL(bpull_kernel, dim3(grid), dim3(kBThreads), 0, st, pa);
         CSBFS_HIP(hipGetLastError());
@@ -1056,74 +1066,73 @@ extern "C" int csbfs_batch_bfs(csbfs_batch_engine *e, const int64_t *roots, int3
         CSBFS_HIP(hipGetLastError());
         if (ev) CSBFS_HIP(hipEventRecord(ev[1], st));
         BUpdateArgs ua{e->vn, e->f, level, (int32_t)(j + 1), (int32_t)B, n,
-                       e->rootc + sn * Bm, e->ctl + sn, e->qcount, (int32_t)P, fc,
+                       e->rootc(sn), e->ctl(sn), e->qcount, (int32_t)P, fc,
                        e->fm, g->deg, e->dstate->sums};
         hipLaunchKernelGGL(bupdate_kernel, dim3(grid_for((words + kBTile - 1) / kBTile, kBThreads / 64, 2048)), dim3(kBThreads), 0, st, ua);
         CSBFS_HIP(hipGetLastError());
-        // direction of the next level's expansion, from the update's sums
-        hipLaunchKernelGGL(bdir_kernel, dim3(1), dim3(1), 0, st, e->dstate, j + 1 < e->L ? e->dirs + j + 1 : nullptr,
-                           n, kBatchAlpha, kBatchBeta);
-        CSBFS_HIP(hipGetLastError());
         if (ev) CSBFS_HIP(hipEventRecord(ev[2], st));
-        const int hs = (int)((j + 1) & 1);
-        CSBFS_HIP(hipMemcpyAsync(e->host_ctl + hs, e->ctl + sn, sizeof(unsigned long long),
-                                 hipMemcpyDeviceToHost, st));
-        CSBFS_HIP(hipEventRecord(e->count_ev[hs], st));
         return CSBFS_OK;
     };
 
+    // the size of level k's frontier, posted by its encode (polled)
+    auto wait_count = [&](int64_t k, unsigned long long *cnt) -> int {
+        const unsigned long long want = (unsigned long long)k & ((1ull << (64 - kPostBits)) - 1);
+        volatile unsigned long long *word = e->host_ctl + (k & 1);
+        for (uint64_t spins = 1;; ++spins) {
+            hipError_t q = hipErrorNotReady;
+            // a failed launch never writes the word: ask the stream now and then
+            if ((spins & 0x3ff) == 0) q = hipStreamQuery(st);
+            if (q != hipSuccess && q != hipErrorNotReady) return hip_fail(q, "batch stream", __FILE__, __LINE__);
+            const unsigned long long v = *word;  // read after the query: a drained stream has posted
+            if ((v >> kPostBits) == want) {
+                *cnt = v & ((1ull << kPostBits) - 1);
+                return CSBFS_OK;
+            }
+            if (q == hipSuccess) return fail(CSBFS_ECORRUPT, "csbfs_batch_bfs: a level's frontier size never arrived");
+        }
+    };
     rc = enqueue_iter(0);
     if (rc) return rc;
     int64_t k = 0;
     for (;; ++k) {
+        // the size is posted by the first kernel of iteration k + 1; the rest
+        // of that iteration hides the host's answer
         rc = enqueue_iter(k + 1);
         if (rc) return rc;
-        const int hs = (int)((k + 1) & 1);
-        CSBFS_HIP(hipEventSynchronize(e->count_ev[hs]));
-        if (e->host_ctl[hs] == 0) break;
+        unsigned long long cnt = 0;
+        rc = wait_count(k + 1, &cnt);
+        if (rc) {
+            (void)hipStreamSynchronize(st);
+            return rc;
+        }
+        if (cnt == 0) break;
     }
     const int64_t nl = k + 1;
     *n_levels = (int32_t)(nl < INT32_MAX ? nl : INT32_MAX);
     e->last_levels = *n_levels;
     e->last_roots = (int32_t)B;
 
-    int32_t hstatus = 0;
-    CSBFS_HIP(hipMemcpyAsync(&hstatus, e->status, sizeof(hstatus), hipMemcpyDeviceToHost, st));
+    // status and statistics: the header and the records of the levels wanted
     const int64_t have = nl < e->L ? nl : e->L;
     const int64_t want = stats_cap < have ? stats_cap : have;
-    std::vector<unsigned long long> rootc, ed, sb, uw;
-    std::vector<int64_t> wd;
-    std::vector<int32_t> dr;
-    if (want > 0) {
-        dr.resize(want);
-        CSBFS_HIP(hipMemcpyAsync(dr.data(), e->dirs, sizeof(int32_t) * want, hipMemcpyDeviceToHost, st));
-        rootc.resize(want * Bm);
-        ed.resize(want);
-        sb.resize(want * e->Smax);
-        uw.resize(want * Bm * P);
-        wd.resize(want * e->Smax);
-        CSBFS_HIP(hipMemcpyAsync(rootc.data(), e->rootc, sizeof(unsigned long long) * want * Bm, hipMemcpyDeviceToHost, st));
-        CSBFS_HIP(hipMemcpyAsync(ed.data(), e->edges, sizeof(unsigned long long) * want, hipMemcpyDeviceToHost, st));
-        CSBFS_HIP(hipMemcpyAsync(sb.data(), e->sbits, sizeof(unsigned long long) * want * e->Smax, hipMemcpyDeviceToHost, st));
-        CSBFS_HIP(hipMemcpyAsync(uw.data(), e->uwords, sizeof(unsigned long long) * want * Bm * P, hipMemcpyDeviceToHost, st));
-        CSBFS_HIP(hipMemcpyAsync(wd.data(), e->words, sizeof(int64_t) * want * e->Smax, hipMemcpyDeviceToHost, st));
-    }
+    std::vector<unsigned long long> rec((size_t)(e->hdr + want * e->stride));
+    CSBFS_HIP(hipMemcpyAsync(rec.data(), e->zero_mem, 8 * rec.size(), hipMemcpyDeviceToHost, st));
     CSBFS_HIP(hipStreamSynchronize(st));
+    const int32_t hstatus = (int32_t)rec[0];
     if (hstatus != 0) {
-        // an encode that gave up waiting may have left look-back state behind
-        CSBFS_HIP(hipMemsetAsync(e->look, 0, e->look_bytes, st));
-        CSBFS_HIP(hipStreamSynchronize(st));
         if (hstatus == 1) return fail(CSBFS_ECORRUPT, "csbfs_batch_bfs: a stream failed validation while decoding");
         return fail(CSBFS_ECORRUPT, "csbfs_batch_bfs: internal consistency check failed");
     }
     for (int64_t lv = 0; lv < want; ++lv) {
         csbfs_level_stats &s = stats[lv];
         s = csbfs_level_stats{};
-        s.edges = (int64_t)ed[lv];
-        s.direction = dr[lv];
+        const unsigned long long *r0 = rec.data() + e->hdr + lv * e->stride;
+        const unsigned long long *rootc = r0 + 3, *uw = rootc + Bm, *sb = uw + Bm * P, *wd = sb + e->Smax;
+        s.edges = (int64_t)r0[1];
+        s.direction = (int32_t)r0[2];
         std::vector<int64_t> send(P, 0), recv(P, 0);
         for (int64_t r = 0; r < B; ++r) {
-            const int64_t fr = (int64_t)rootc[lv * Bm + r];
+            const int64_t fr = (int64_t)rootc[r];
             if (fr == 0) continue;
             s.frontier += fr;
             if (lv == 0) {
@@ -1133,18 +1142,18 @@ extern "C" int csbfs_batch_bfs(csbfs_batch_engine *e, const int64_t *roots, int3
             s.unsieved_bits += (P - 1) * fr;
             s.raw_bytes += P * (P - 1) * 8 * W;
             for (int64_t i = 0; i < P; ++i) {
-                s.wah_unsieved_bytes += 8 * (P - 1) * (int64_t)uw[lv * Bm * P + r * P + i];
+                s.wah_unsieved_bytes += 8 * (P - 1) * (int64_t)uw[r * P + i];
                 for (int64_t j = 0; j < P; ++j) {
-                    const int64_t sidx = lv * e->Smax + (r * P + i) * P + j;
+                    const int64_t sidx = (r * P + i) * P + j;
                     s.view_bits += (int64_t)sb[sidx];
                     if (i == j) {
-                        s.self_bytes += 8 * wd[sidx];
+                        s.self_bytes += 8 * (int64_t)wd[sidx];
                         continue;
                     }
                     s.sieved_bits += (int64_t)sb[sidx];
-                    s.wah_sieved_bytes += 8 * wd[sidx];
-                    send[i] += 8 * wd[sidx];
-                    recv[j] += 8 * wd[sidx];
+                    s.wah_sieved_bytes += 8 * (int64_t)wd[sidx];
+                    send[i] += 8 * (int64_t)wd[sidx];
+                    recv[j] += 8 * (int64_t)wd[sidx];
                 }
             }
         }
@@ -1176,17 +1185,17 @@ extern "C" int csbfs_batch_stream_words(const csbfs_batch_engine *e, int32_t *wo
     if (!e || !words || cap_levels < 0) return fail(CSBFS_EINVAL, "csbfs_batch_stream_words: bad argument");
     const int64_t P = e->g->P, B = e->last_roots, Bm = e->Bmax;
     const int64_t lv_have = std::min<int64_t>(e->L, e->last_levels);
-    std::vector<int64_t> wd((size_t)(lv_have > 0 ? lv_have : 1) * e->Smax);
-    std::vector<unsigned long long> rc((size_t)(lv_have > 0 ? lv_have : 1) * Bm);
-    if (lv_have > 0) {
-        CSBFS_HIP(hipMemcpy(wd.data(), e->words, sizeof(int64_t) * lv_have * e->Smax, hipMemcpyDeviceToHost));
-        CSBFS_HIP(hipMemcpy(rc.data(), e->rootc, sizeof(unsigned long long) * lv_have * Bm, hipMemcpyDeviceToHost));
-    }
+    std::vector<unsigned long long> rec((size_t)(lv_have * e->stride) + 1);
+    if (lv_have > 0)
+        CSBFS_HIP(hipMemcpy(rec.data(), e->ctl(0), sizeof(unsigned long long) * lv_have * e->stride,
+                            hipMemcpyDeviceToHost));
+    const int64_t words_at = 3 + Bm + Bm * P + e->Smax;
     for (int64_t lv = 0; lv < cap_levels; ++lv)
         for (int64_t r = 0; r < B; ++r)
             for (int64_t s = 0; s < P * P; ++s) {
-                const bool live = lv > 0 && lv < lv_have && rc[lv * Bm + r] > 0;
-                words[(lv * B + r) * P * P + s] = live ? (int32_t)wd[lv * e->Smax + r * P * P + s] : 0;
+                const unsigned long long *r0 = rec.data() + lv * e->stride;
+                const bool live = lv > 0 && lv < lv_have && r0[3 + r] > 0;
+                words[(lv * B + r) * P * P + s] = live ? (int32_t)r0[words_at + r * P * P + s] : 0;
             }
     return CSBFS_OK;
 }
@@ -1205,8 +1214,8 @@ extern "C" int csbfs_batch_copy_stream(const csbfs_batch_engine *e, int32_t k, i
     hipStream_t st = as_stream(stream);
     int64_t nw = 0;
     unsigned long long fr = 0;
-    CSBFS_HIP(hipMemcpyAsync(&fr, e->rootc + (int64_t)k * e->Bmax + r, sizeof(fr), hipMemcpyDeviceToHost, st));
-    CSBFS_HIP(hipMemcpyAsync(&nw, e->words + (int64_t)k * e->Smax + s, sizeof(int64_t), hipMemcpyDeviceToHost, st));
+    CSBFS_HIP(hipMemcpyAsync(&fr, e->rootc(k) + r, sizeof(fr), hipMemcpyDeviceToHost, st));
+    CSBFS_HIP(hipMemcpyAsync(&nw, e->words(k) + s, sizeof(int64_t), hipMemcpyDeviceToHost, st));
     CSBFS_HIP(hipStreamSynchronize(st));
     if (k == 0 || fr == 0) nw = 0;  // no message carries level 0 or an empty frontier
     *n_words_out = nw;

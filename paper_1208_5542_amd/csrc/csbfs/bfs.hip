@@ -1280,55 +1280,54 @@ struct SeedArgs {
     int64_t zero_words;
     uint32_t *look;      // encoder look-back words and tickets (any contents in a new workspace)
     int64_t look_words;
-    uint32_t *marks;     // both levels' segment marks [2 * nmarks]
+    uint32_t *marks;     // both levels' segment marks [2 * nmarks], level 0's first
     int64_t mark_words;
+    int64_t root;
+    int64_t one_word, dir_word;  // words of `zero` that hold |f^0| = 1 and level 0's direction
+    const int32_t *deg;
+    DirState *ds;
+    int32_t dir0;
 };
 
-__global__ void seed_fill_kernel(SeedArgs a) {
+// Everything a search starts from, in one pass: cleared state, and f(s) <- s
+// (the source is known to every processor without a message; its block is
+// marked, so its views are scanned and later cleared). A second launch of one
+// thread for the source cost 5 us of every search.
+__global__ void seed_kernel(SeedArgs a) {
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     int64_t top = a.n > a.view_words ? a.n : a.view_words;
     top = top > a.zero_words ? top : a.zero_words;
     top = top > a.look_words ? top : a.look_words;
     top = top > a.mark_words ? top : a.mark_words;
+    const int64_t rw = a.root >> 6;
+    const uint64_t bit = 1ull << (a.root & 63);
     for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < top; k += stride) {
-        if (k < a.zero_words) a.zero[k] = 0;
+        if (k < a.zero_words) a.zero[k] = k == a.one_word ? 1u : k == a.dir_word ? (uint32_t)a.dir0 : 0u;
         if (k < a.look_words) a.look[k] = 0;
-        if (k < a.mark_words) a.marks[k] = 0;
+        if (k < a.mark_words) a.marks[k] = k == rw >> kMarkShift;
         if (k < a.n) {
-            a.level[k] = -1;
-            a.parent[k] = -1;
+            a.level[k] = k == a.root ? 0 : -1;
+            a.parent[k] = k == a.root ? (int32_t)k : -1;
         }
         if (k < a.words) {
-            a.pi[k] = 0;
+            a.pi[k] = k == rw ? bit : 0;
             a.N0[k] = 0;
             a.N1[k] = 0;
         }
-        if (k < a.view_words) a.view[k] = 0;
+        // every processor's views are one n-bit map, so the source is at one
+        // word of each
+        if (k < a.view_words) a.view[k] = (uint32_t)k % (uint32_t)a.words == (uint32_t)rw ? bit : 0;
+        if (k == 0) {
+            DirState s;
+            s.cur = a.dir0;
+            s.tile = 64;
+            s.bin = 0;
+            s.spare = 0;
+            s.vdeg = (unsigned long long)a.deg[a.root];
+            s.prev = 1;
+            *a.ds = s;
+        }
     }
-}
-
-// f(s) <- s: the source is known to every processor without a message.
-__global__ void seed_root_kernel(SeedArgs a, int64_t root, int64_t R, int64_t W, int32_t P,
-                                 unsigned long long *ctl0, unsigned long long *rank0,
-                                 const int32_t *deg, DirState *ds, int32_t *rec0, int32_t dir0,
-                                 BlockMarks marks0) {
-    const int64_t own = root / R, rl = root - own * R;
-    DirState s;
-    s.cur = dir0;
-    s.tile = 64;
-    s.bin = 0;
-    s.spare = 0;
-    s.vdeg = (unsigned long long)deg[root];
-    s.prev = 1;
-    *ds = s;
-    *rec0 = dir0;
-    a.level[root] = 0;
-    a.parent[root] = (int32_t)root;
-    a.pi[root >> 6] |= 1ull << (root & 63);
-    for (int32_t i = 0; i < P; ++i) a.view[((int64_t)i * P + own) * W + (rl >> 6)] |= 1ull << (rl & 63);
-    marks0.mark_word(root >> 6);  // f^0's block, so its views are scanned and later cleared
-    ctl0[0] = 1;
-    rank0[own] = 1;
 }
 
 
@@ -1341,18 +1340,28 @@ using namespace csbfs;
 namespace csbfs {
 namespace {
 
-// Per-level device counters, slot k for k < L and slot L for levels past the
-// workspace's capacity (reset before each use).
+// Per-level device counters: one record of `stride` words per level, slot k
+// for k < L and slot L for levels past the workspace's capacity (reset before
+// each use). A record lies in one piece, and the header (status) before the
+// first, so that the host reads a search's statistics with one copy. The sums
+// that every workgroup adds to have a 128-byte line each (atomics on one line
+// are serialized).
+constexpr int64_t kLine = 16;  // words
 struct LevelCounters {
-    unsigned long long *ctl;     // [L+1][2]: |f^k|, sum of degrees over f^k
-    unsigned long long *rank;    // [L+1][P]
-    unsigned long long *edges;   // [L+1]
-    unsigned long long *pulled;  // [L+1]
-    unsigned long long *sbits;   // [L+1][S]
-    unsigned long long *uwords;  // [L+1][P]
-    int64_t *words;              // [L+1][S]
-    int32_t *dir;                // [L+1]: direction used to expand f^k
+    unsigned long long *base;
+    int64_t stride, S;
+    __host__ __device__ unsigned long long *at(int64_t slot) const { return base + slot * stride; }
+    unsigned long long *ctl(int64_t k) const { return at(k); }        // [2]: |f^k|, sum of degrees over f^k
+    unsigned long long *edges(int64_t k) const { return at(k) + kLine; }
+    unsigned long long *pulled(int64_t k) const { return at(k) + 2 * kLine; }
+    int32_t *dir(int64_t k) const { return (int32_t *)(at(k) + 2); }  // direction used to expand f^k
+    int64_t *words(int64_t k) const { return (int64_t *)(at(k) + 3 * kLine); }      // [S]
+    unsigned long long *sbits(int64_t k) const { return at(k) + 3 * kLine + S; }       // [S]
+    unsigned long long *uwords(int64_t k) const { return at(k) + 3 * kLine + 2 * S; }  // [P]
 };
+constexpr int64_t rec_words(int64_t S, int64_t P) { return (3 * kLine + 2 * S + P + kLine - 1) / kLine * kLine; }
+// header: entries a pull found, the status flag, the chunk-queue counts
+constexpr int64_t hdr_words(int64_t P) { return kLine + ((P + 1) / 2 + kLine - 1) / kLine * kLine; }
 
 // Where every buffer of one search lives inside its workspace, and the
 // search's parameters; a function of (n, p, adjacency total, config) only.
@@ -1481,10 +1490,9 @@ int search_layout(int64_t n, int32_t p, int64_t nnz, const csbfs_search_config *
     y.bpairs = take(8 * y.nbins * kBinGrid * y.cseg);
     y.bseg = take(4 * y.nbins * kBinGrid);
     // everything a search starts from zero, in one block the seed clears:
-    // per-level counters, then the status flag and the queue counts
+    // the header (status flag, queue counts), then the per-level counters
     const int64_t slots = y.L + 1;
-    y.counters_bytes = 8 + 8 * slots * (2 + y.P + 1 + 1 + y.S + y.P) + 8 * slots * y.S + 4 * slots + 4 * (2 + y.P);
-    y.counters_bytes = (y.counters_bytes + 3) / 4 * 4;
+    y.counters_bytes = 8 * (hdr_words(y.P) + slots * rec_words(y.S, y.P));
     y.counters = take(y.counters_bytes);
     y.total = o;
     *out = y;
@@ -1508,25 +1516,11 @@ SearchState bind_workspace(const SearchLayout &y, void *ws) {
     w.marks[0] = (uint32_t *)(b + y.marks);
     w.marks[1] = w.marks[0] + y.nmarks;
     w.counters_mem = b + y.counters;
-    const int64_t slots = y.L + 1, P = y.P, S = y.S;
     unsigned long long *c = (unsigned long long *)w.counters_mem;
-    w.exp_mf = c++;
-    w.lc.ctl = c;
-    c += slots * 2;
-    w.lc.rank = c;
-    c += slots * P;
-    w.lc.edges = c;
-    c += slots;
-    w.lc.pulled = c;
-    c += slots;
-    w.lc.sbits = c;
-    c += slots * S;
-    w.lc.uwords = c;
-    c += slots * P;
-    w.lc.words = (int64_t *)c;
-    w.lc.dir = (int32_t *)(w.lc.words + slots * S);
-    w.status = w.lc.dir + slots;
-    w.ctrs = reinterpret_cast<uint32_t *>(w.status + 1);
+    w.exp_mf = c;
+    w.status = (int32_t *)(c + 1);
+    w.ctrs = (uint32_t *)(c + kLine);
+    w.lc = LevelCounters{c + hdr_words(y.P), rec_words(y.S, y.P), y.S};
     w.bpairs = (uint64_t *)(b + y.bpairs);
     w.bseg = (uint32_t *)(b + y.bseg);
     return w;
@@ -1535,13 +1529,7 @@ SearchState bind_workspace(const SearchLayout &y, void *ws) {
 inline int64_t slot_of(const SearchLayout &y, int64_t k) { return k < y.L ? k : y.L; }
 
 int reset_overflow_slot(const SearchLayout &y, const SearchState &w, hipStream_t st) {
-    const int64_t L = y.L, P = y.P, S = y.S;
-    CSBFS_HIP(hipMemsetAsync(w.lc.ctl + 2 * L, 0, 2 * sizeof(unsigned long long), st));
-    CSBFS_HIP(hipMemsetAsync(w.lc.rank + L * P, 0, sizeof(unsigned long long) * P, st));
-    CSBFS_HIP(hipMemsetAsync(w.lc.edges + L, 0, sizeof(unsigned long long), st));
-    CSBFS_HIP(hipMemsetAsync(w.lc.pulled + L, 0, sizeof(unsigned long long), st));
-    CSBFS_HIP(hipMemsetAsync(w.lc.sbits + L * S, 0, sizeof(unsigned long long) * S, st));
-    CSBFS_HIP(hipMemsetAsync(w.lc.uwords + L * P, 0, sizeof(unsigned long long) * P, st));
+    CSBFS_HIP(hipMemsetAsync(w.lc.at(y.L), 0, 8 * w.lc.stride, st));
     return CSBFS_OK;
 }
 
@@ -1581,7 +1569,7 @@ int wait_count(const Mailbox &mb, const SearchLayout &y, const SearchState &w, i
         }
     }
     unsigned long long v = 0;
-    CSBFS_HIP(hipMemcpyAsync(&v, w.lc.ctl + 2 * slot_of(y, k), sizeof(v), hipMemcpyDeviceToHost, st));
+    CSBFS_HIP(hipMemcpyAsync(&v, w.lc.ctl(slot_of(y, k)), sizeof(v), hipMemcpyDeviceToHost, st));
     CSBFS_HIP(hipStreamSynchronize(st));
     *cnt = v;
     return CSBFS_OK;
@@ -1612,16 +1600,14 @@ int run_search(const csbfs_graph *g, const SearchLayout &y, const SearchState &w
         mb.host[1] = 0;
     }
     // a0: seed (also clears the counters and the encoder's look-back state)
+    auto marks_of = [&](int64_t k) { return BlockMarks{w.marks[k & 1]}; };
+    const int64_t one_word = 2 * hdr_words(P);  // the first record's |f^0|, in 32-bit words
     SeedArgs sa{level, parent, w.pi, w.nb[0], w.nb[1], w.view, n, words, view_words,
                 (uint32_t *)w.counters_mem, y.counters_bytes / 4, (uint32_t *)w.look, y.look_bytes / 4,
-                w.marks[0], 2 * y.nmarks};
-    auto marks_of = [&](int64_t k) { return BlockMarks{w.marks[k & 1]}; };
+                w.marks[0], 2 * y.nmarks, root, one_word, one_word + 4, (const int32_t *)g->deg, w.dstate, dir0};
     int64_t fill_items = n > view_words ? n : view_words;
     fill_items = fill_items > y.look_bytes / 4 ? fill_items : y.look_bytes / 4;
-    hipLaunchKernelGGL(seed_fill_kernel, dim3(grid_for(fill_items, 256, 8192)), dim3(256), 0, st, sa);
-    CSBFS_HIP(hipGetLastError());
-    hipLaunchKernelGGL(seed_root_kernel, dim3(1), dim3(1), 0, st, sa, root, R, W, (int32_t)P, w.lc.ctl, w.lc.rank,
-                       (const int32_t *)g->deg, w.dstate, w.lc.dir, dir0, marks_of(0));
+    hipLaunchKernelGGL(seed_kernel, dim3(grid_for(fill_items, 256, 8192)), dim3(256), 0, st, sa);
     CSBFS_HIP(hipGetLastError());
 
     ExpandArgs ea{};
@@ -1729,9 +1715,9 @@ int run_search(const csbfs_graph *g, const SearchLayout &y, const SearchState &w
             // a2 + a4 + a5: t = S & ~pi, levels, sieve and compress every stream i -> j
             const int64_t arena_slot = keep ? sj : 0;
             wb.out_base = w.arena + arena_slot * S * y.cap;
-            wb.n_words = w.lc.words + sj * S;
-            wb.stat_sieved_bits = w.lc.sbits + sj * S;
-            wb.stat_unsieved_words = w.lc.uwords + sj * P;
+            wb.n_words = w.lc.words(sj);
+            wb.stat_sieved_bits = w.lc.sbits(sj);
+            wb.stat_unsieved_words = w.lc.uwords(sj);
             FrontierHook fh{w.nb[j & 1], w.nb[(j + 1) & 1], w.pi, w.view, level, g->deg, w.part,
                             marks_of(j), marks_of(j + 1), W, y.seg_words, (int32_t)P, (int32_t)j, 1, 1};
             if (y.enc_gpt == 2)
@@ -1744,8 +1730,8 @@ int run_search(const csbfs_graph *g, const SearchLayout &y, const SearchState &w
             if (ev) CSBFS_HIP(hipEventRecord(ev[1], st));
             // a6: the stream slots are the receive buffers; a7: decode into the
             // views; a3: reduction of |f^j|, direction of its expansion
-            da.rec = w.lc.dir + sj;
-            ReduceArgs ra{w.part, S * y.nseg, w.lc.ctl + 2 * sj, mb.dev ? mb.dev + (j & 1) : nullptr, w.ctrs,
+            da.rec = w.lc.dir(sj);
+            ReduceArgs ra{w.part, S * y.nseg, w.lc.ctl(sj), mb.dev ? mb.dev + (j & 1) : nullptr, w.ctrs,
                           (int32_t)P, (int32_t)j, w.marks[(j + 1) & 1], y.nmarks, w.exp_mf, da};
             hipLaunchKernelGGL(search_decode_kernel, dec_grid, dim3(kDecThreads), 0, st, wb, ra);
             CSBFS_HIP(hipGetLastError());
@@ -1765,7 +1751,7 @@ int run_search(const csbfs_graph *g, const SearchLayout &y, const SearchState &w
         pa.marks_next = marks_of(j + 1);
         pb.marks_next = marks_of(j + 1);
         // a1: expand f^j (tile width and direction chosen on the device)
-        ea.edges = w.lc.edges + sj;
+        ea.edges = w.lc.edges(sj);
         if (dense) {
             hipLaunchKernelGGL(expand_kernel<true>, dim3(exp_grid), dim3(kExpThreads), 0, st, ea);
             CSBFS_HIP(hipGetLastError());
@@ -1785,8 +1771,8 @@ int run_search(const csbfs_graph *g, const SearchLayout &y, const SearchState &w
                 CSBFS_HIP(hipGetLastError());
             }
         } else {
-            pb.edges = w.lc.edges + sj;
-            pb.pulled = w.lc.pulled + sj;
+            pb.edges = w.lc.edges(sj);
+            pb.pulled = w.lc.pulled(sj);
             if (bu_only) {
                 PullArgs pbu = pb;
                 pbu.xcd = bu_xcd;
@@ -1815,17 +1801,16 @@ int run_search(const csbfs_graph *g, const SearchLayout &y, const SearchState &w
     };
 
     // The host reads |f^k| (posted by the decode of level k) while the
-    // expansion of level k and iteration k + 1 are already queued. When f^k
-    // is empty the decode chose the idle direction: the expansion of level k
-    // and every kernel of iteration k + 1 return at once, and their counters
-    // lie past the last reported level.
+    // expansion of f^k runs, which hides its answer. When f^k is empty the
+    // decode chose the idle direction: that expansion returns at once, and its
+    // counters lie past the last reported level. (With iteration k + 1 queued
+    // ahead its four idle launches ended every search: scale 20 Erdos-Renyi
+    // 390 us against 384, scale 22 418 us a search against 412.)
     int rc = enqueue_iter(0);
-    if (rc) return rc;
-    rc = enqueue_iter(1);
     if (rc) return rc;
     int64_t k = 1;
     for (;;) {
-        rc = enqueue_iter(k + 1);
+        rc = enqueue_iter(k);
         if (rc) return rc;
         unsigned long long cnt = 0;
         rc = wait_count(mb, y, w, k, st, &cnt);
@@ -1842,37 +1827,14 @@ int run_search(const csbfs_graph *g, const SearchLayout &y, const SearchState &w
     const int64_t nl = k;  // levels 0..k-1
     *n_levels = (int32_t)(nl < INT32_MAX ? nl : INT32_MAX);
 
-    // statistics
-    int32_t hstatus = 0;
-    CSBFS_HIP(hipMemcpyAsync(&hstatus, w.status, sizeof(hstatus), hipMemcpyDeviceToHost, st));
+    // status and statistics: the header and the records of the levels wanted
     const int64_t have = nl < y.L ? nl : y.L;
     const int64_t want = stats_cap < have ? stats_cap : have;
-    std::vector<unsigned long long> ctl, ed, sb, uw, pl;
-    std::vector<int64_t> wd;
-    std::vector<int32_t> dr;
-    if (want > 0) {
-        ctl.resize(2 * want);
-        ed.resize(want);
-        pl.resize(want);
-        dr.resize(want);
-        sb.resize(want * S);
-        uw.resize(want * P);
-        wd.resize(want * S);
-        CSBFS_HIP(hipMemcpyAsync(pl.data(), w.lc.pulled, sizeof(unsigned long long) * want,
-                                 hipMemcpyDeviceToHost, st));
-        CSBFS_HIP(hipMemcpyAsync(dr.data(), w.lc.dir, sizeof(int32_t) * want, hipMemcpyDeviceToHost, st));
-        CSBFS_HIP(hipMemcpyAsync(ctl.data(), w.lc.ctl, sizeof(unsigned long long) * 2 * want,
-                                 hipMemcpyDeviceToHost, st));
-        CSBFS_HIP(hipMemcpyAsync(ed.data(), w.lc.edges, sizeof(unsigned long long) * want,
-                                 hipMemcpyDeviceToHost, st));
-        CSBFS_HIP(hipMemcpyAsync(sb.data(), w.lc.sbits, sizeof(unsigned long long) * want * S,
-                                 hipMemcpyDeviceToHost, st));
-        CSBFS_HIP(hipMemcpyAsync(uw.data(), w.lc.uwords, sizeof(unsigned long long) * want * P,
-                                 hipMemcpyDeviceToHost, st));
-        CSBFS_HIP(hipMemcpyAsync(wd.data(), w.lc.words, sizeof(int64_t) * want * S,
-                                 hipMemcpyDeviceToHost, st));
-    }
+    const int64_t rs = w.lc.stride, hw = hdr_words(P);
+    std::vector<unsigned long long> rec((size_t)(hw + want * rs));
+    CSBFS_HIP(hipMemcpyAsync(rec.data(), w.counters_mem, 8 * rec.size(), hipMemcpyDeviceToHost, st));
     CSBFS_HIP(hipStreamSynchronize(st));
+    const int32_t hstatus = (int32_t)rec[1];
     if (hstatus != 0) {
         if (hstatus == 1) return fail(CSBFS_ECORRUPT, "csbfs_bfs: a stream failed validation while decoding");
         return fail(CSBFS_ECORRUPT, "csbfs_bfs: internal consistency check failed");
@@ -1880,31 +1842,34 @@ int run_search(const csbfs_graph *g, const SearchLayout &y, const SearchState &w
     for (int64_t lv = 0; lv < want; ++lv) {
         csbfs_level_stats &s = stats[lv];
         s = csbfs_level_stats{};
-        s.frontier = (int64_t)ctl[2 * lv];
-        s.edges = (int64_t)ed[lv];
-        s.pulled = (int64_t)pl[lv];
-        s.direction = dr[lv] & 0xFF;
-        s.push = dr[lv] >> 8;
+        const unsigned long long *rc0 = rec.data() + hw + lv * rs;
+        const unsigned long long *wd = rc0 + 3 * kLine, *sb = wd + S, *uw = sb + S;
+        const int32_t dr = (int32_t)rc0[2];
+        s.frontier = (int64_t)rc0[0];
+        s.edges = (int64_t)rc0[kLine];
+        s.pulled = (int64_t)rc0[2 * kLine];
+        s.direction = dr & 0xFF;
+        s.push = dr >> 8;
         s.view_bits = P;  // the source is set in every view at level 0
         if (lv > 0) {
             int64_t sieved = 0, sent = 0, self = 0, uws = 0, maxr = 0;
             s.view_bits = 0;
-            for (int64_t q = 0; q < S; ++q) s.view_bits += (int64_t)sb[lv * S + q];
+            for (int64_t q = 0; q < S; ++q) s.view_bits += (int64_t)sb[q];
             for (int64_t i = 0; i < P; ++i) {
                 int64_t send = 0, recv = 0;
                 for (int64_t j = 0; j < P; ++j) {
-                    const int64_t w_ij = wd[lv * S + i * P + j];
-                    const int64_t w_ji = wd[lv * S + j * P + i];
+                    const int64_t w_ij = (int64_t)wd[i * P + j];
+                    const int64_t w_ji = (int64_t)wd[j * P + i];
                     if (i == j) {
                         self += 8 * w_ij;
                         continue;
                     }
-                    sieved += (int64_t)sb[lv * S + i * P + j];
+                    sieved += (int64_t)sb[i * P + j];
                     sent += 8 * w_ij;
                     send += 8 * w_ij;
                     recv += 8 * w_ji;
                 }
-                uws += (int64_t)uw[lv * P + i];
+                uws += (int64_t)uw[i];
                 if (send + recv > maxr) maxr = send + recv;
             }
             s.sieved_bits = sieved;
@@ -1938,15 +1903,17 @@ int run_search(const csbfs_graph *g, const SearchLayout &y, const SearchState &w
 
 int stream_words_of(const SearchLayout &y, const SearchState &w, int32_t last_levels, int32_t *words,
                     int32_t cap_levels, hipStream_t st) {
-    const int64_t S = y.S;
+    const int64_t S = y.S, rs = w.lc.stride;
     const int64_t have = std::min<int64_t>(std::min<int64_t>(cap_levels, last_levels), y.L);
-    std::vector<int64_t> wd((size_t)(have > 0 ? have : 1) * S);
+    std::vector<int64_t> wd((size_t)(have > 0 ? have : 1) * rs);
     if (have > 0) {
-        CSBFS_HIP(hipMemcpyAsync(wd.data(), w.lc.words, sizeof(int64_t) * have * S, hipMemcpyDeviceToHost, st));
+        // the words of each record, up to the last one's
+        CSBFS_HIP(hipMemcpyAsync(wd.data(), w.lc.words(0), sizeof(int64_t) * ((have - 1) * rs + S), hipMemcpyDeviceToHost,
+                                 st));
         CSBFS_HIP(hipStreamSynchronize(st));
     }
     for (int64_t lv = 0; lv < cap_levels; ++lv)
-        for (int64_t s = 0; s < S; ++s) words[lv * S + s] = lv < have ? (int32_t)wd[lv * S + s] : 0;
+        for (int64_t s = 0; s < S; ++s) words[lv * S + s] = lv < have ? (int32_t)wd[lv * rs + s] : 0;
     return CSBFS_OK;
 }
 
@@ -1958,7 +1925,7 @@ int copy_stream_of(const SearchLayout &y, const SearchState &w, int32_t last_lev
         return fail(CSBFS_EINVAL, "copy stream: level or processor out of range");
     const int64_t s = (int64_t)i * y.P + j;
     int64_t nw = 0;
-    CSBFS_HIP(hipMemcpyAsync(&nw, w.lc.words + (int64_t)k * y.S + s, sizeof(int64_t), hipMemcpyDeviceToHost, st));
+    CSBFS_HIP(hipMemcpyAsync(&nw, w.lc.words(k) + s, sizeof(int64_t), hipMemcpyDeviceToHost, st));
     CSBFS_HIP(hipStreamSynchronize(st));
     *n_words_out = nw;
     if (nw > cap_words) return fail(CSBFS_ENOSPACE, "copy stream: dst too small");
