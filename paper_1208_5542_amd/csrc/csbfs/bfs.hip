@@ -1360,8 +1360,17 @@ struct LevelCounters {
     unsigned long long *uwords(int64_t k) const { return at(k) + 3 * kLine + 2 * S; }  // [P]
 };
 constexpr int64_t rec_words(int64_t S, int64_t P) { return (3 * kLine + 2 * S + P + kLine - 1) / kLine * kLine; }
-// header: entries a pull found, the status flag, the chunk-queue counts
+// header: entries a pull found, the status flag, the number of levels (one-
+// launch searches); the chunk-queue counts from the next line on
 constexpr int64_t hdr_words(int64_t P) { return kLine + ((P + 1) / 2 + kLine - 1) / kLine * kLine; }
+
+}  // namespace
+}  // namespace csbfs
+
+#include "bfs_small.hpp"
+
+namespace csbfs {
+namespace {
 
 // Where every buffer of one search lives inside its workspace, and the
 // search's parameters; a function of (n, p, adjacency total, config) only.
@@ -1370,6 +1379,7 @@ struct SearchLayout {
     int64_t nbins, cseg, bin_cap;  // binned push: bins, pairs per segment, pairs in all
     unsigned long long bin_min, bin_deg, bin_limit;  // a level's entries: at least, per frontier vertex, at most
     int enc_gpt;  // groups per encoder thread: segments of 512 * enc_gpt groups
+    bool enc_fixed;  // ... as the caller asked
     uint32_t flags;
     float alpha, beta;
     // byte offsets
@@ -1428,6 +1438,7 @@ int search_layout(int64_t n, int32_t p, int64_t nnz, const csbfs_search_config *
     y.S = (int64_t)p * p;
     y.cap = wah_cap(y.R);
     y.enc_gpt = c.segment_groups == 1024 ? 2 : c.segment_groups == 2048 ? 4 : search_enc_gpt(y.R, y.S);
+    y.enc_fixed = c.segment_groups != 0;
     y.nseg = enc_segments(y.R, y.enc_gpt);
     y.seg_words = (int64_t)kEncThreads * y.enc_gpt * kGroupBits / 64;
     y.nchunk = dec_chunks(y.R);
@@ -1575,6 +1586,74 @@ int wait_count(const Mailbox &mb, const SearchLayout &y, const SearchState &w, i
     return CSBFS_OK;
 }
 
+// Status and statistics of a search from its header and `want` level records.
+int finish_search(const SearchLayout &y, const std::vector<unsigned long long> &rec, int64_t hw, int64_t rs, int64_t want,
+                  int64_t P, int64_t W, csbfs_level_stats *stats) {
+    const int64_t S = y.S;
+    const int32_t hstatus = (int32_t)rec[1];
+    if (hstatus != 0) {
+        if (hstatus == 1) return fail(CSBFS_ECORRUPT, "csbfs_bfs: a stream failed validation while decoding");
+        return fail(CSBFS_ECORRUPT, "csbfs_bfs: internal consistency check failed");
+    }
+    for (int64_t lv = 0; lv < want; ++lv) {
+        csbfs_level_stats &s = stats[lv];
+        s = csbfs_level_stats{};
+        const unsigned long long *rc0 = rec.data() + hw + lv * rs;
+        const unsigned long long *wd = rc0 + 3 * kLine, *sb = wd + S, *uw = sb + S;
+        const int32_t dr = (int32_t)rc0[2];
+        s.frontier = (int64_t)rc0[0];
+        s.edges = (int64_t)rc0[kLine];
+        s.pulled = (int64_t)rc0[2 * kLine];
+        s.direction = dr & 0xFF;
+        s.push = dr >> 8;
+        s.view_bits = P;  // the source is set in every view at level 0
+        if (lv > 0) {
+            int64_t sieved = 0, sent = 0, self = 0, uws = 0, maxr = 0;
+            s.view_bits = 0;
+            for (int64_t q = 0; q < S; ++q) s.view_bits += (int64_t)sb[q];
+            for (int64_t i = 0; i < P; ++i) {
+                int64_t send = 0, recv = 0;
+                for (int64_t j = 0; j < P; ++j) {
+                    const int64_t w_ij = (int64_t)wd[i * P + j];
+                    const int64_t w_ji = (int64_t)wd[j * P + i];
+                    if (i == j) {
+                        self += 8 * w_ij;
+                        continue;
+                    }
+                    sieved += (int64_t)sb[i * P + j];
+                    sent += 8 * w_ij;
+                    send += 8 * w_ij;
+                    recv += 8 * w_ji;
+                }
+                uws += (int64_t)uw[i];
+                if (send + recv > maxr) maxr = send + recv;
+            }
+            s.sieved_bits = sieved;
+            s.unsieved_bits = (P - 1) * s.frontier;
+            s.raw_bytes = P * (P - 1) * 8 * W;
+            s.wah_unsieved_bytes = 8 * (P - 1) * uws;
+            s.wah_sieved_bytes = sent;
+            s.self_bytes = self;
+            s.max_rank_bytes = maxr;
+        }
+    }
+    return CSBFS_OK;
+}
+
+// Searches that one workgroup makes in one launch (small_search_kernel): the
+// state fits LDS and the adjacency is short enough for one CU. The limit lies
+// where the level-by-level kernels' time (220 to 260 us, launches mostly) is
+// reached: with 2^19 entries (R-MAT scale 14) 128 us, with 580k (uniform,
+// 16128 vertices) 196 us against 251, with 2^20 222 us against 234 (R-MAT
+// scale 15) and 284 against 257 (uniform, 25600 vertices). The dense
+// evaluation, per-kernel timing, a binned push and a fixed encoder segment
+// ask for the level-by-level kernels.
+constexpr int64_t kSmallNnz = int64_t(3) << 18;
+bool small_search(const SearchLayout &y, const csbfs_graph *g, const SmallLds &l, bool dense, bool timing) {
+    return !dense && !timing && y.nbins == 0 && !y.enc_fixed && g->nnz <= kSmallNnz && g->n <= (1 << 15) &&
+           8 * (int64_t)l.total <= 160 * 1024 - 1024;
+}
+
 constexpr int kEvPerLevel2 = kEvPerLevel;
 
 // One search from root on workspace state w (Algorithm 3 level loop).
@@ -1598,6 +1677,54 @@ int run_search(const csbfs_graph *g, const SearchLayout &y, const SearchState &w
     if (mb.host) {
         mb.host[0] = 0;  // level tags start at 1
         mb.host[1] = 0;
+    }
+    DirArgs da{};
+    da.st = w.dstate;
+    da.n = n;
+    da.nnz = g->nnz;
+    da.alpha = y.alpha;
+    da.beta = y.beta;
+    da.force = force;
+    da.bin_min = y.bin_min;
+    da.bin_deg = y.bin_deg;
+    da.bin_cap = y.bin_limit;
+
+    // the header and the records of the first `count` levels
+    const int64_t rs = w.lc.stride, hw = hdr_words(P);
+    std::vector<unsigned long long> rec;
+    auto read_records = [&](int64_t count) -> int {
+        rec.resize((size_t)(hw + count * rs));
+        CSBFS_HIP(hipMemcpyAsync(rec.data(), w.counters_mem, 8 * rec.size(), hipMemcpyDeviceToHost, st));
+        CSBFS_HIP(hipStreamSynchronize(st));
+        return CSBFS_OK;
+    };
+    auto levels_wanted = [&](int64_t nl) { return std::min<int64_t>(stats_cap, std::min<int64_t>(nl, y.L)); };
+    int64_t nl = 0;
+    const SmallLds sl = small_lds(n, P);
+    if (small_search(y, g, sl, dense, timing)) {
+        SmallArgs sa{sl, (int32_t)n, (int32_t)R, (int32_t)W, (int32_t)P, (int32_t)root, g->row_ptr, g->col_base, g->col,
+                     (y.flags & CSBFS_FLAG_NO_SIEVE) ? nullptr : g->dir, g->deg, g->live, g->pull_off, g->pull_col,
+                     g->head, level, parent, w.arena, y.cap, keep ? S * y.cap : 0,
+                     (unsigned long long *)w.counters_mem, w.lc, y.L, mb.dev, da, dir0};
+        hipLaunchKernelGGL(small_search_kernel, dim3(1), dim3(kSmallThreads), 8 * (size_t)sl.total, st, sa);
+        CSBFS_HIP(hipGetLastError());
+        if (mb.host && stats_cap == 0) {
+            // everything the host needs is in the mailbox
+            CSBFS_HIP(hipStreamSynchronize(st));
+            const unsigned long long v = mb.host[0];
+            rec.assign((size_t)hw, 0);
+            rec[1] = v >> 32;
+            nl = (int64_t)(v & 0xffffffffull);
+        } else {
+            // most searches have no more levels than the first copy brings
+            int rc = read_records(levels_wanted(16));
+            if (rc) return rc;
+            nl = (int64_t)rec[2];
+            if (levels_wanted(nl) > levels_wanted(16)) rc = read_records(levels_wanted(nl));
+            if (rc) return rc;
+        }
+        *n_levels = (int32_t)nl;
+        return finish_search(y, rec, hw, rs, levels_wanted(nl), P, W, stats);
     }
     // a0: seed (also clears the counters and the encoder's look-back state)
     auto marks_of = [&](int64_t k) { return BlockMarks{w.marks[k & 1]}; };
@@ -1668,17 +1795,6 @@ int run_search(const csbfs_graph *g, const SearchLayout &y, const SearchState &w
     pa.xcd = xcd_split(P, pull_grid) && W % kPullTileDense == 0;
     pb.xcd = xcd_split(P, exp_grid) && xcd_split(P, level_grid) && W % kPullTileBU == 0;
     const int32_t bu_xcd = xcd_split(P, bu_grid) && W % kPullTileBU == 0;
-    DirArgs da{};
-    da.st = w.dstate;
-    da.n = n;
-    da.nnz = g->nnz;
-    da.alpha = y.alpha;
-    da.beta = y.beta;
-    da.force = force;
-    da.bin_min = y.bin_min;
-    da.bin_deg = y.bin_deg;
-    da.bin_cap = y.bin_limit;
-
     WahBatch wb{};  // the words come from FrontierHook, not from a bits buffer
     wb.mask_base = (y.flags & CSBFS_FLAG_NO_SIEVE) ? nullptr : g->dir;
     wb.nbits = R;
@@ -1824,63 +1940,12 @@ int run_search(const csbfs_graph *g, const SearchLayout &y, const SearchState &w
             return fail(CSBFS_ECORRUPT, "csbfs_bfs: frontier counts did not reach zero");
         }
     }
-    const int64_t nl = k;  // levels 0..k-1
+    nl = k;  // levels 0..k-1
     *n_levels = (int32_t)(nl < INT32_MAX ? nl : INT32_MAX);
-
-    // status and statistics: the header and the records of the levels wanted
-    const int64_t have = nl < y.L ? nl : y.L;
-    const int64_t want = stats_cap < have ? stats_cap : have;
-    const int64_t rs = w.lc.stride, hw = hdr_words(P);
-    std::vector<unsigned long long> rec((size_t)(hw + want * rs));
-    CSBFS_HIP(hipMemcpyAsync(rec.data(), w.counters_mem, 8 * rec.size(), hipMemcpyDeviceToHost, st));
-    CSBFS_HIP(hipStreamSynchronize(st));
-    const int32_t hstatus = (int32_t)rec[1];
-    if (hstatus != 0) {
-        if (hstatus == 1) return fail(CSBFS_ECORRUPT, "csbfs_bfs: a stream failed validation while decoding");
-        return fail(CSBFS_ECORRUPT, "csbfs_bfs: internal consistency check failed");
-    }
-    for (int64_t lv = 0; lv < want; ++lv) {
-        csbfs_level_stats &s = stats[lv];
-        s = csbfs_level_stats{};
-        const unsigned long long *rc0 = rec.data() + hw + lv * rs;
-        const unsigned long long *wd = rc0 + 3 * kLine, *sb = wd + S, *uw = sb + S;
-        const int32_t dr = (int32_t)rc0[2];
-        s.frontier = (int64_t)rc0[0];
-        s.edges = (int64_t)rc0[kLine];
-        s.pulled = (int64_t)rc0[2 * kLine];
-        s.direction = dr & 0xFF;
-        s.push = dr >> 8;
-        s.view_bits = P;  // the source is set in every view at level 0
-        if (lv > 0) {
-            int64_t sieved = 0, sent = 0, self = 0, uws = 0, maxr = 0;
-            s.view_bits = 0;
-            for (int64_t q = 0; q < S; ++q) s.view_bits += (int64_t)sb[q];
-            for (int64_t i = 0; i < P; ++i) {
-                int64_t send = 0, recv = 0;
-                for (int64_t j = 0; j < P; ++j) {
-                    const int64_t w_ij = (int64_t)wd[i * P + j];
-                    const int64_t w_ji = (int64_t)wd[j * P + i];
-                    if (i == j) {
-                        self += 8 * w_ij;
-                        continue;
-                    }
-                    sieved += (int64_t)sb[i * P + j];
-                    sent += 8 * w_ij;
-                    send += 8 * w_ij;
-                    recv += 8 * w_ji;
-                }
-                uws += (int64_t)uw[i];
-                if (send + recv > maxr) maxr = send + recv;
-            }
-            s.sieved_bits = sieved;
-            s.unsieved_bits = (P - 1) * s.frontier;
-            s.raw_bytes = P * (P - 1) * 8 * W;
-            s.wah_unsieved_bytes = 8 * (P - 1) * uws;
-            s.wah_sieved_bytes = sent;
-            s.self_bytes = self;
-            s.max_rank_bytes = maxr;
-        }
-    }
+    const int64_t want = levels_wanted(nl);
+    rc = read_records(want);
+    if (!rc) rc = finish_search(y, rec, hw, rs, want, P, W, stats);
+    if (rc) return rc;
     if (timing) {
         // the update of f^k runs inside its encoder: ms_update stays 0 and
         // ms_compress holds update + sieve + compress of level k
