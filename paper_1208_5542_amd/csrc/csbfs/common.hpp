@@ -86,9 +86,8 @@ struct WahBatch {
     unsigned long long *look;   // device [S * nseg]
     uint32_t *ticket;           // device [kTicketStride * S]
     int64_t nseg;
-    // decoder scratch: per (stream, chunk) group totals, or (chunk_starts)
-    // the first group of each chunk, recorded by the encoder: the decoder
-    // then runs one pass and checks that consecutive chunks meet
+    // the first group of each (stream, chunk), recorded by the encoder (if
+    // chunk_starts) for the decoder, which checks that consecutive chunks meet
     int64_t *chunk_groups;      // device [S * nchunk]
     int64_t nchunk;
     int32_t chunk_starts;

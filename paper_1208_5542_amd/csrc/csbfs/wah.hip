@@ -1,6 +1,7 @@
 // WAH-64 sieve + compress and decompress kernels (Sec. IV, Table 3; Alg. 3
 // sieve, Compress and Uncompress), batched over the p * p streams of a level;
 // the device code is in wah_device.hpp.
+#include <algorithm>
 #include <mutex>
 
 #include "wah_device.hpp"
@@ -13,7 +14,78 @@ __global__ __launch_bounds__(kEncThreads) void wah_encode_kernel(WahBatch b) {
     encode_segment<kEncGpt>(b, h, blockIdx.y, blockIdx.x == 0);
 }
 
-__global__ __launch_bounds__(kDecThreads) void wah_dec_count(WahBatch b) { dec_count_body(b); }
+// A stream from elsewhere, in one pass over it (a pass that summed every
+// chunk's groups first, two clears and a copy of the length from the host made
+// it 50 us for the smallest streams, now 30 with the caller's read of the
+// status; 2^28 bits 89 us, now 78). Chunks are taken in ticket order, so every awaited
+// one runs; a chunk publishes its group total (state 1), then the total
+// through it (state 2), each in one 64-bit word whose top two bits are the
+// state. Totals above G (an invalid stream) are cut off at G + 1.
+struct DecodeArgs {
+    const uint64_t *words;
+    int64_t nw, nbits, nchunk;
+    uint64_t *dst;
+    int32_t *status;
+    unsigned long long *look;  // [nchunk], zero (unused with one chunk)
+    uint32_t *ticket;          // zero
+};
+constexpr int kDecWide = 2;
+constexpr int64_t kDecWideWords = 512 * kDecChunk;
+constexpr uint64_t kDlAgg = 1ull << 62, kDlInc = 2ull << 62, kDlValue = kDlAgg - 1;
+
+__device__ long long dec_prefix(const DecodeArgs &a, int64_t c) {
+    const int lane = threadIdx.x & 63;
+    long long sum = 0;
+    for (int64_t k0 = c - 1;; k0 -= 64) {
+        const int64_t k = k0 - lane;
+        uint64_t v = k >= 0 ? __hip_atomic_load(&a.look[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : kDlInc;
+        uint32_t polls = 0;
+        while (__ballot((v >> 62) == 0)) {
+            if (++polls == kLbSpinLimit) {  // a lost publication: flag the stream, stop waiting
+                if (lane == 0) *a.status = 1;
+                if ((v >> 62) == 0) v = kDlInc;
+                break;
+            }
+            if ((v >> 62) == 0) v = __hip_atomic_load(&a.look[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        const uint64_t inc = __ballot((v >> 62) == 2);
+        const int stop = inc ? __ffsll((unsigned long long)inc) - 1 : 63;
+        sum += (long long)readlane64((uint64_t)wave_incl_scan_i64(lane <= stop ? (long long)(v & kDlValue) : 0), 63);
+        if (inc) return sum;
+    }
+}
+
+template <int kT>
+__global__ __launch_bounds__(kDecThreads) void wah_decode_kernel(DecodeArgs a) {
+    __shared__ int64_t sh_c;
+    __shared__ long long sh_before;
+    const int64_t G = a.nbits / kGroupBits, r = a.nbits - G * kGroupBits;
+    if (threadIdx.x == 0) {
+        sh_c = a.nchunk > 1 ? (int64_t)atomicAdd(a.ticket, 1u) : 0;
+        if (a.nchunk <= 1) *a.status = 0;  // else cleared by the launch before
+    }
+    __syncthreads();
+    const int64_t c = sh_c;
+    if (c == 0 && threadIdx.x == 0) dec_tail(a.words, a.nw, a.nw, a.nbits, G, r, a.dst, a.status);
+    if (c * kT * kDecChunk >= a.nw - (r > 0 ? 1 : 0)) return;
+    dec_chunk<kT>(a.words, a.nw, G, r, c, a.dst, a.status, [&](long long total) -> long long {
+        if (a.nchunk <= 1) return 0;
+        const long long cut = G + 1;
+        if (threadIdx.x < 64) {
+            const long long mine = total < cut ? total : cut;
+            if (threadIdx.x == 0 && c > 0)
+                __hip_atomic_store(&a.look[c], (uint64_t)mine | kDlAgg, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const long long before = c > 0 ? dec_prefix(a, c) : 0;
+            if (threadIdx.x == 0) {
+                const long long all = before + mine < cut ? before + mine : cut;
+                __hip_atomic_store(&a.look[c], (uint64_t)all | kDlInc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                sh_before = before;
+            }
+        }
+        __syncthreads();
+        return sh_before;
+    });
+}
 
 __global__ __launch_bounds__(kDecThreads) void wah_dec_scatter(WahBatch b) { dec_scatter_body(b); }
 
@@ -26,6 +98,16 @@ __global__ void zero_words_kernel(uint32_t *p, int64_t words) {
 }
 
 __global__ void store_i64_kernel(int64_t *p, int64_t v) { *p = v; }
+__global__ void store_i32_kernel(int32_t *p, int32_t v) { *p = v; }
+
+__global__ void clear_decode_kernel(DecodeArgs a) {
+    const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    for (int64_t k = t; k < a.nchunk; k += (int64_t)gridDim.x * blockDim.x) a.look[k] = 0;
+    if (t == 0) {
+        *a.ticket = 0;
+        *a.status = 0;
+    }
+}
 
 }  // namespace
 
@@ -41,10 +123,6 @@ int launch_wah_encode(const WahBatch &b, hipStream_t stream) {
 int launch_wah_decode(const WahBatch &b, hipStream_t stream) {
     const int64_t S = batch_streams(b);
     dim3 grid((unsigned)b.nchunk, (unsigned)S);
-    if (!b.chunk_starts) {
-        hipLaunchKernelGGL(wah_dec_count, grid, dim3(kDecThreads), 0, stream, b);
-        CSBFS_HIP(hipGetLastError());
-    }
     hipLaunchKernelGGL(wah_dec_scatter, grid, dim3(kDecThreads), 0, stream, b);
     CSBFS_HIP(hipGetLastError());
     return CSBFS_OK;
@@ -60,7 +138,7 @@ namespace {
 constexpr size_t kAlign = 256;
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 struct WsLayout {
-    size_t look, ticket, chunk_groups, n_words, total;
+    size_t look, ticket, dec_look, dec_ticket, total;  // encoder's, then decoder's look-back words and tickets
 };
 WsLayout ws_layout(int64_t nbits) {
     WsLayout l;
@@ -68,9 +146,9 @@ WsLayout ws_layout(int64_t nbits) {
     const int64_t nchunk = dec_chunks(nbits);
     l.look = 0;
     l.ticket = l.look + align_up(sizeof(unsigned long long) * nseg);
-    l.chunk_groups = l.ticket + align_up(sizeof(uint32_t) * kTicketStride);
-    l.n_words = l.chunk_groups + align_up(sizeof(int64_t) * nchunk);
-    l.total = l.n_words + align_up(sizeof(int64_t));
+    l.dec_look = l.ticket + align_up(sizeof(uint32_t) * kTicketStride);
+    l.dec_ticket = l.dec_look + align_up(sizeof(unsigned long long) * nchunk);
+    l.total = l.dec_ticket + align_up(sizeof(uint32_t));
     return l;
 }
 }  // namespace
@@ -111,7 +189,7 @@ extern "C" int csbfs_wah_encode(const uint64_t *bits, const uint64_t *mask, int6
     }
     // the look-back words and tickets start at zero (the caller's workspace
     // may hold anything)
-    CSBFS_HIP(hipMemsetAsync(ws + l.look, 0, l.chunk_groups - l.look, as_stream(stream)));
+    CSBFS_HIP(hipMemsetAsync(ws + l.look, 0, l.dec_look - l.look, as_stream(stream)));
     return launch_wah_encode(b, as_stream(stream));
 }
 
@@ -153,7 +231,7 @@ extern "C" int64_t csbfs_wah_noalloc_max_bits(void) {
     while (lo < hi) {
         const int64_t mid = lo + (hi - lo + 1) / 2;
         const WsLayout l = ws_layout(mid);
-        if (l.chunk_groups <= kNoAllocScratchBytes)
+        if (l.dec_look <= kNoAllocScratchBytes)
             lo = mid;
         else
             hi = mid - 1;
@@ -183,7 +261,7 @@ extern "C" int csbfs_wah_encode_noalloc(const uint64_t *bits, const uint64_t *ma
     char *ws = (char *)ptr;
     // look-back words and tickets start at zero; the previous call on this
     // device left them zero unless it failed, so clear them every time
-    const int64_t words = (int64_t)((l.chunk_groups - l.look) / 4);
+    const int64_t words = (int64_t)((l.dec_look - l.look) / 4);
     hipLaunchKernelGGL(zero_words_kernel, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, st,
                        (uint32_t *)(ws + l.look), words);
     CSBFS_HIP(hipGetLastError());
@@ -213,38 +291,28 @@ extern "C" int csbfs_wah_decode_or(const uint64_t *words, int64_t n_words, int64
     const WsLayout l = ws_layout(nbits);
     if (ws_bytes < l.total) return fail(CSBFS_ENOSPACE, "csbfs_wah_decode_or: workspace too small");
     hipStream_t st = as_stream(stream);
-    CSBFS_HIP(hipMemsetAsync(status, 0, sizeof(int32_t), st));
-    if (n_words > wah_cap(nbits)) {
-        const int32_t one = 1;
-        CSBFS_HIP(hipMemcpyAsync(status, &one, sizeof(one), hipMemcpyHostToDevice, st));
-        CSBFS_HIP(hipStreamSynchronize(st));
-        return CSBFS_OK;
-    }
-    if (nbits == 0) {
-        if (n_words != 0) {
-            const int32_t one = 1;
-            CSBFS_HIP(hipMemcpyAsync(status, &one, sizeof(one), hipMemcpyHostToDevice, st));
-            CSBFS_HIP(hipStreamSynchronize(st));
-        }
+    // a length no stream of nbits bits has (and an empty stream of none, which
+    // is valid)
+    if (n_words > wah_cap(nbits) || nbits == 0) {
+        hipLaunchKernelGGL(store_i32_kernel, dim3(1), dim3(1), 0, st, status, n_words != 0 ? 1 : 0);
+        CSBFS_HIP(hipGetLastError());
         return CSBFS_OK;
     }
     char *ws = (char *)workspace;
-    int64_t *nw_dev = (int64_t *)(ws + l.n_words);
-    CSBFS_HIP(hipMemcpyAsync(nw_dev, &n_words, sizeof(int64_t), hipMemcpyHostToDevice, st));
-    WahBatch b{};
-    b.out_base = const_cast<uint64_t *>(words);
-    b.n_words = nw_dev;
-    b.nbits = nbits;
-    b.words_per_piece = (nbits + 63) / 64;
-    b.cap = n_words > 0 ? n_words : 1;
-    b.P = 1;
-    b.chunk_groups = (int64_t *)(ws + l.chunk_groups);
-    b.nchunk = dec_chunks(nbits);
-    b.dst_base = dst;
-    b.status = status;
-    int rc = launch_wah_decode(b, st);
-    if (rc != CSBFS_OK) return rc;
-    // the host-to-device copies above read stack memory: finish before returning
-    CSBFS_HIP(hipStreamSynchronize(st));
+    // kDecChunk words per workgroup while that many workgroups fit the GPU, else
+    // twice that (a ticket costs 5 ns, in sequence: 2^28 bits took 67 us with
+    // 4158 of them and 47 with half; four or eight times were no faster)
+    const int64_t per = n_words <= kDecWideWords ? kDecChunk : kDecWide * kDecChunk;
+    DecodeArgs a{words, n_words, nbits, std::max<int64_t>((n_words + per - 1) / per, 1), dst, status,
+                 (unsigned long long *)(ws + l.dec_look), (uint32_t *)(ws + l.dec_ticket)};
+    if (a.nchunk > 1) {
+        hipLaunchKernelGGL(clear_decode_kernel, dim3(grid_for(a.nchunk, 256, 1024)), dim3(256), 0, st, a);
+        CSBFS_HIP(hipGetLastError());
+    }
+    if (per == kDecChunk)
+        hipLaunchKernelGGL(wah_decode_kernel<1>, dim3((unsigned)a.nchunk), dim3(kDecThreads), 0, st, a);
+    else
+        hipLaunchKernelGGL(wah_decode_kernel<kDecWide>, dim3((unsigned)a.nchunk), dim3(kDecThreads), 0, st, a);
+    CSBFS_HIP(hipGetLastError());
     return CSBFS_OK;
 }

@@ -17,13 +17,13 @@
 // is applied while the segment is staged into LDS, so the sieved piece is
 // never written to memory.
 //
-// Decoder. dec_scatter_body gives every word its first group by a block scan
+// Decoder. dec_chunk gives every word its first group by a block scan
 // from its chunk's first group, and ORs literal and 1-fill
 // bits into the destination (0-fills write nothing: the destination starts
 // zeroed). A chunk of kDecChunk words learns its first group from the
 // encoder, which records it while writing the chunk's first word (searches),
-// or from a first pass (dec_count_body) that sums the groups of every chunk
-// (streams from elsewhere). Every stream is validated: zero-length fills,
+// or by a decoupled look-back over the earlier chunks' group totals (streams
+// from elsewhere). Every stream is validated: zero-length fills,
 // group totals that do not match floor(N/63), chunks that do not meet, or
 // active-word bits above r set the status flag.
 #include "device.hpp"
@@ -52,26 +52,6 @@ __device__ int block_excl_scan(int v, int *total) {
     __syncthreads();
     int before = wid > 0 ? wsum[wid - 1] : 0;
     *total = wsum[nw - 1];
-    __syncthreads();
-    return before + incl - v;
-}
-
-__device__ long long block_excl_scan64(long long v, long long *total) {
-    __shared__ long long wsum64[16];
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wid = threadIdx.x / kWave;
-    const int nw = blockDim.x / kWave;
-    long long incl = wave_incl_scan_i64(v);
-    if (lane == kWave - 1) wsum64[wid] = incl;
-    __syncthreads();
-    if (wid == 0) {
-        long long s = lane < nw ? wsum64[lane] : 0;
-        s = wave_incl_scan_i64(s);
-        if (lane < nw) wsum64[lane] = s;
-    }
-    __syncthreads();
-    long long before = wid > 0 ? wsum64[wid - 1] : 0;
-    *total = wsum64[nw - 1];
     __syncthreads();
     return before + incl - v;
 }
@@ -527,9 +507,7 @@ __device__ void fill_ones(uint64_t *dst, int64_t lo, int64_t hi) {
     }
 }
 
-// The same two helpers on a workgroup's LDS copy of a range of words.
-constexpr int kDecLdsWords = 2048;
-
+// The same two helpers on words in LDS.
 __device__ __forceinline__ void or_bits_lds(unsigned long long *buf, int64_t bit, uint64_t v, int nbits) {
     const int64_t q = bit >> 6;
     const int sh = (int)(bit & 63);
@@ -555,33 +533,160 @@ __device__ void fill_ones_lds(unsigned long long *buf, int64_t lo, int64_t hi) {
     }
 }
 
-__device__ __forceinline__ void dec_count_body(const WahBatch &b) {
-    const int64_t c = blockIdx.x;
-    const int64_t s = blockIdx.y;
-    if (plane_skipped(b, s)) return;
-    const int64_t G = b.nbits / kGroupBits;
-    const int64_t r = b.nbits - G * kGroupBits;
-    const int64_t nw = stream_words(b, s);
+// One chunk of a stream: kT * kDecChunk words of `words` (nw in all, G groups
+// and an active word of r bits) into dst. `start(total)` gives the chunk's
+// first group, block-uniform, once the chunk's group total is known to all
+// threads.
+//
+// The chunk's groups [g0, g1) fill output words [q0, q1]. When they fit LDS
+// (always for literal words) they are laid out there, one 63-bit group a slot
+// with plain stores, and every output word is put together from the two
+// groups it spans and stored once; only the two end words, which neighbouring
+// chunks also touch, need global atomics. Bound by memory: the stream is read
+// once and dst read and written once. Chunks whose fills span more groups OR
+// straight into dst.
+constexpr int dec_lds_groups(int t) { return t == 1 ? 2 * kDecChunk : t * kDecChunk + kDecChunk; }
+
+template <int kT, class Start>
+__device__ __forceinline__ void dec_chunk(const uint64_t *words, int64_t nw, int64_t G, int64_t r, int64_t c,
+                                          uint64_t *dst, int32_t *status, Start start) {
+    constexpr int kWaves = kDecThreads / 64, kLds = dec_lds_groups(kT);
+    static_assert(kT * kWaves <= 64 && kDecWpt == 2, "one wave total per lane of the second scan");
+    __shared__ long long wtot[kT * kWaves + 1];
+    __shared__ uint64_t grp[kLds];
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     const int64_t nreg = nw - (r > 0 ? 1 : 0);
-    const uint64_t *words = b.out_base + s * b.cap;
-    long long groups = 0;
+    const int64_t wa = c * kT * kDecChunk + (int64_t)threadIdx.x * kDecWpt;  // words wa, wa + 1 of each kDecChunk
+    uint64_t v[kT][kDecWpt];
+    long long g[kT][kDecWpt], excl[kT];
     bool bad = false;
-    const int64_t w0 = c * kDecChunk;
-    for (int64_t w = w0 + threadIdx.x; w < w0 + kDecChunk && w < nreg; w += blockDim.x) {
-        const uint64_t v = words[w];
-        if (v & kFillFlag) {
-            const uint64_t cnt = v & kCountMask;
-            if (cnt == 0 || cnt > (uint64_t)G) bad = true;
-            groups += (long long)cnt;
-        } else {
-            groups += 1;
+#pragma unroll
+    for (int t = 0; t < kT; ++t)
+#pragma unroll
+        for (int k = 0; k < kDecWpt; ++k) {
+            const int64_t w = wa + t * kDecChunk + k;
+            v[t][k] = w < nreg ? words[w] : 0;
+        }
+#pragma unroll
+    for (int t = 0; t < kT; ++t) {
+        long long mine = 0;
+#pragma unroll
+        for (int k = 0; k < kDecWpt; ++k) {
+            g[t][k] = 0;
+            if (wa + t * kDecChunk + k < nreg) {
+                const uint64_t cnt = (v[t][k] & kFillFlag) ? v[t][k] & kCountMask : 1;
+                if (cnt == 0 || cnt > (uint64_t)G)
+                    bad = true;  // its groups are left out: the totals stay small
+                else
+                    g[t][k] = (long long)cnt;
+                mine += g[t][k];
+            }
+        }
+        const long long incl = wave_incl_scan_i64(mine);
+        excl[t] = incl - mine;
+        if (lane == 63) wtot[t * kWaves + wid] = incl;
+    }
+    __syncthreads();
+    if (wid == 0) {
+        const long long x = lane < kT * kWaves ? wtot[lane] : 0;
+        const long long incl = wave_incl_scan_i64(x);
+        if (lane < kT * kWaves) wtot[lane] = incl - x;
+        if (lane == 63) wtot[kT * kWaves] = incl;
+    }
+    __syncthreads();
+    const long long chunk_total = wtot[kT * kWaves];
+    const long long before = start(chunk_total);
+    if (before < 0 || before > G) {
+        if (threadIdx.x == 0) *status = 1;
+        return;
+    }
+    const long long g0 = before, g1 = before + chunk_total;
+    const bool staged = g1 > g0 && g1 <= G && g1 - g0 <= kLds;
+    if (staged) {
+        for (int k = threadIdx.x; k < (int)(g1 - g0); k += kDecThreads) grp[k] = 0;
+        __syncthreads();
+    }
+#pragma unroll
+    for (int t = 0; t < kT; ++t) {
+        long long x = before + wtot[t * kWaves + wid] + excl[t];
+#pragma unroll
+        for (int k = 0; k < kDecWpt; ++k) {
+            const int64_t w = wa + t * kDecChunk + k;
+            if (w >= nreg || bad) continue;
+            if (x + g[t][k] > G) {
+                bad = true;
+                continue;
+            }
+            if (!(v[t][k] & kFillFlag)) {
+                const uint64_t bits = __builtin_bitreverse64(v[t][k]) >> 1;
+                if (staged)
+                    grp[x - g0] = bits;
+                else if (bits)
+                    or_bits(dst, x * kGroupBits, bits, kGroupBits);
+            } else if (v[t][k] & kFillBit) {
+                if (staged)
+                    for (long long q = 0; q < g[t][k]; ++q) grp[x - g0 + q] = kMask63;
+                else
+                    fill_ones(dst, x * kGroupBits, (x + g[t][k]) * kGroupBits);
+            }
+            x += g[t][k];
+            if (w == nreg - 1 && x != G) bad = true;
         }
     }
-    groups = block_reduce(groups, SumI64(), 0LL);
-    if (bad) *b.status = 1;
-    if (threadIdx.x == 0) b.chunk_groups[s * b.nchunk + c] = groups;
+    if (bad) *status = 1;
+    if (staged) {
+        __syncthreads();
+        constexpr int kUn = 4;  // words whose old values are loaded together
+        const int64_t q0 = (g0 * kGroupBits) >> 6, q1 = (g1 * kGroupBits - 1) >> 6;
+        const int ng = (int)(g1 - g0), nq = (int)(q1 - q0) + 1;
+        const int lead = (int)(g0 * kGroupBits - q0 * 64);  // bits of word q0 before group g0
+        for (int k0 = threadIdx.x; k0 < nq; k0 += kUn * kDecThreads) {
+            uint64_t val[kUn], old[kUn];
+#pragma unroll
+            for (int m = 0; m < kUn; ++m) {
+                const int k = k0 + m * kDecThreads;
+                const int p = k * 64 - lead;  // word's first bit, from group g0's
+                val[m] = 0;
+                if (p < 0) {
+                    val[m] = grp[0] << -p;  // group g0 reaches the end of its first word
+                } else if (k < nq) {
+                    const int a = p / kGroupBits, o = p - a * kGroupBits;
+                    val[m] = grp[a] >> o;
+                    if (a + 1 < ng) val[m] |= grp[a + 1] << (kGroupBits - o);
+                }
+                old[m] = val[m] && k > 0 && k < nq - 1 ? dst[q0 + k] : 0;
+            }
+#pragma unroll
+            for (int m = 0; m < kUn; ++m) {
+                const int k = k0 + m * kDecThreads;
+                if (!val[m]) continue;
+                if (k == 0 || k == nq - 1)
+                    atomicOr((unsigned long long *)&dst[q0 + k], (unsigned long long)val[m]);
+                else
+                    dst[q0 + k] = old[m] | val[m];  // no other workgroup writes an inner word
+            }
+        }
+    }
 }
 
+// Stream-wide checks and the active word, by one thread of the stream.
+__device__ __forceinline__ void dec_tail(const uint64_t *words, int64_t nw, int64_t cap, int64_t nbits, int64_t G,
+                                         int64_t r, uint64_t *dst, int32_t *status) {
+    const int64_t nreg = nw - (r > 0 ? 1 : 0);
+    if (nw < 0 || nreg < 0 || (nw == 0 && nbits > 0) || nw > cap) {
+        *status = 1;
+    } else if (r > 0) {
+        const uint64_t a = words[nw - 1];
+        if (a >> r)
+            *status = 1;
+        else if (a)
+            or_bits(dst, G * kGroupBits, __builtin_bitreverse64(a) >> (64 - r), (int)r);
+    }
+    if (nreg == 0 && G != 0) *status = 1;
+}
+
+// Chunk c of stream blockIdx.y of a batch, its first group recorded by the
+// encoder.
 __device__ __forceinline__ void dec_scatter_body(const WahBatch &b, int64_t c = -1) {
     if (c < 0) c = blockIdx.x;
     const int64_t s = blockIdx.y;
@@ -594,109 +699,15 @@ __device__ __forceinline__ void dec_scatter_body(const WahBatch &b, int64_t c = 
     const int64_t nreg = nw - (r > 0 ? 1 : 0);
     const uint64_t *words = b.out_base + s * b.cap;
     uint64_t *dst = b.dst_base + si.r * b.dst_plane_stride + (j * b.P + i) * b.words_per_piece;
-    const int64_t w0 = c * kDecChunk;
-
-    if (c == 0 && threadIdx.x == 0) {
-        if (nw < 0 || nreg < 0 || (nw == 0 && b.nbits > 0) || nw > b.cap) {
-            *b.status = 1;
-        } else if (r > 0) {
-            const uint64_t a = words[nw - 1];
-            if (a >> r) {
-                *b.status = 1;
-            } else if (a) {
-                const uint64_t v = __builtin_bitreverse64(a) >> (64 - r);
-                or_bits(dst, G * kGroupBits, v, (int)r);
-            }
-        }
-        if (nreg == 0 && G != 0) *b.status = 1;
-    }
-    if (nw < 0 || nw > b.cap || w0 >= nreg) return;
-
-    long long before = 0;
-    if (b.chunk_starts) {
-        before = c > 0 ? b.chunk_groups[s * b.nchunk + c] : 0;
-        if (before < 0 || before > G) {
-            if (threadIdx.x == 0) *b.status = 1;
-            return;
-        }
-    } else {
-        for (int64_t k = threadIdx.x; k < c; k += blockDim.x) before += b.chunk_groups[s * b.nchunk + k];
-        before = block_reduce(before, SumI64(), 0LL);
-    }
-
-    uint64_t v[kDecWpt];
-    long long g[kDecWpt];
-    long long mine = 0;
-    const int64_t wa = w0 + (int64_t)threadIdx.x * kDecWpt;
-    for (int k = 0; k < kDecWpt; ++k) {
-        const int64_t w = wa + k;
-        g[k] = 0;
-        if (w < nreg) {
-            v[k] = words[w];
-            g[k] = (v[k] & kFillFlag) ? (long long)(v[k] & kCountMask) : 1;
-            mine += g[k];
-        }
-    }
-    long long chunk_total;
-    long long x = before + block_excl_scan64(mine, &chunk_total);
-    // recorded starts: this chunk must end where the next one starts
-    if (b.chunk_starts && threadIdx.x == 0 && w0 + kDecChunk < nreg &&
-        before + chunk_total != b.chunk_groups[s * b.nchunk + c + 1])
-        *b.status = 1;
-
-    // The chunk's groups [g0, g1) fill output words [q0, q1]. When those fit
-    // in LDS (always for literal words: 1024 groups span 1008 words) the
-    // chunk is assembled there and written with one store per word; only
-    // the two end words, which neighbouring chunks also touch, need global
-    // atomics. Chunks whose fills span more words OR straight into dst.
-    __shared__ unsigned long long lbuf[kDecLdsWords];
-    const long long g0 = before, g1 = before + chunk_total;
-    const int64_t q0 = (g0 * kGroupBits) >> 6;
-    const int64_t q1 = g1 > g0 ? (g1 * kGroupBits - 1) >> 6 : q0;
-    const bool staged = g1 > g0 && g1 <= G && q1 - q0 + 1 <= kDecLdsWords;
-    if (staged) {
-        for (int64_t k = threadIdx.x; k <= q1 - q0; k += blockDim.x) lbuf[k] = 0;
-        __syncthreads();
-    }
-    const int64_t base_bit = q0 * 64;
-    bool bad = false;
-    for (int k = 0; k < kDecWpt; ++k) {
-        const int64_t w = wa + k;
-        if (w >= nreg) break;
-        if (g[k] == 0 || x + g[k] > G) {
-            bad = true;
-            break;
-        }
-        if (!(v[k] & kFillFlag)) {
-            const uint64_t bits = __builtin_bitreverse64(v[k]) >> 1;
-            if (bits) {
-                if (staged)
-                    or_bits_lds(lbuf, x * kGroupBits - base_bit, bits, kGroupBits);
-                else
-                    or_bits(dst, x * kGroupBits, bits, kGroupBits);
-            }
-        } else if (v[k] & kFillBit) {
-            if (staged)
-                fill_ones_lds(lbuf, x * kGroupBits - base_bit, (x + g[k]) * kGroupBits - base_bit);
-            else
-                fill_ones(dst, x * kGroupBits, (x + g[k]) * kGroupBits);
-        }
-        x += g[k];
-        if (w == nreg - 1 && x != G) bad = true;
-    }
-    if (bad) *b.status = 1;
-    if (staged) {
-        __syncthreads();
-        for (int64_t k = threadIdx.x; k <= q1 - q0; k += blockDim.x) {
-            const unsigned long long val = lbuf[k];
-            if (!val) continue;
-            const int64_t q = q0 + k;
-            if (q == q0 || q == q1)
-                atomicOr((unsigned long long *)&dst[q], val);
-            else
-                dst[q] |= val;  // no other workgroup writes an inner word
-        }
-    }
+    if (c == 0 && threadIdx.x == 0) dec_tail(words, nw, b.cap, b.nbits, G, r, dst, b.status);
+    if (nw < 0 || nw > b.cap || c * kDecChunk >= nreg) return;
+    const int64_t *starts = b.chunk_groups + s * b.nchunk;
+    dec_chunk<1>(words, nw, G, r, c, dst, b.status, [&](long long total) -> long long {
+        const long long before = c > 0 ? starts[c] : 0;
+        // this chunk must end where the next one starts
+        if (threadIdx.x == 0 && (c + 1) * kDecChunk < nreg && before + total != starts[c + 1]) *b.status = 1;
+        return before;
+    });
 }
 
 }  // namespace
