@@ -188,8 +188,9 @@ extern "C" int csbfs_wah_encode(const uint64_t *bits, const uint64_t *mask, int6
         return CSBFS_OK;
     }
     // the look-back words and tickets start at zero (the caller's workspace
-    // may hold anything)
-    CSBFS_HIP(hipMemsetAsync(ws + l.look, 0, l.dec_look - l.look, as_stream(stream)));
+    // may hold anything); one segment uses neither (up to 129024 bits: 10.5 ->
+    // 8.8 us a call)
+    if (b.nseg > 1) CSBFS_HIP(hipMemsetAsync(ws + l.look, 0, l.dec_look - l.look, as_stream(stream)));
     return launch_wah_encode(b, as_stream(stream));
 }
 
@@ -262,9 +263,11 @@ extern "C" int csbfs_wah_encode_noalloc(const uint64_t *bits, const uint64_t *ma
     // look-back words and tickets start at zero; the previous call on this
     // device left them zero unless it failed, so clear them every time
     const int64_t words = (int64_t)((l.dec_look - l.look) / 4);
-    hipLaunchKernelGGL(zero_words_kernel, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, st,
-                       (uint32_t *)(ws + l.look), words);
-    CSBFS_HIP(hipGetLastError());
+    if (enc_segments(nbits) > 1) {
+        hipLaunchKernelGGL(zero_words_kernel, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, st,
+                           (uint32_t *)(ws + l.look), words);
+        CSBFS_HIP(hipGetLastError());
+    }
     WahBatch b{};
     b.bits_base = bits;
     b.mask_base = mask;

@@ -311,7 +311,8 @@ __device__ __forceinline__ void encode_segment(const WahBatch &b, Hook &hook, in
     }
     // segments in the order the workgroups start, so every awaited one runs
     uint32_t *ticket = b.ticket + s * kTicketStride;  // segments started, over all launches
-    if (threadIdx.x == 0) sh_ticket = atomicAdd(&ticket[0], 1u);
+    // (a stream of one segment awaits nothing: no ticket, a round trip to memory)
+    if (threadIdx.x == 0) sh_ticket = b.nseg > 1 ? atomicAdd(&ticket[0], 1u) : 0u;
     hook.init();
     __syncthreads();
     const uint32_t tk = sh_ticket;
