@@ -854,7 +854,8 @@ int batch_engine_make(const csbfs_graph *g, int32_t max_roots, int32_t max_level
     for (int64_t r = 0; r < P; ++r) qoff[r + 1] = qoff[r] + g->big_items[r];
     const BatchSizes z = batch_sizes(g, B, max_levels, flags);
     if (!mem) {
-        CSBFS_HIP(hipMalloc(&e->mem, (size_t)z.total()));
+        rc = device_malloc(&e->mem, (size_t)z.total());
+        if (rc) return rc;
         e->owns_mem = true;
     } else {
         e->mem = mem;

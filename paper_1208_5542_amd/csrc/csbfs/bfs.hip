@@ -2124,7 +2124,8 @@ extern "C" int csbfs_engine_create(const csbfs_graph *g, int32_t max_levels, uin
     e->cfg.max_levels = max_levels;
     rc = search_layout(g->n, g->P, g->nnz, &e->cfg, &e->y);
     if (rc) return rc;
-    CSBFS_HIP(hipMalloc(&e->ws, (size_t)e->y.total));
+    rc = device_malloc(&e->ws, (size_t)e->y.total);
+    if (rc) return rc;
     e->w = bind_workspace(e->y, e->ws);
     hipError_t herr = hipHostMalloc((void **)&e->mbox, 2 * sizeof(unsigned long long));
     if (herr != hipSuccess) {

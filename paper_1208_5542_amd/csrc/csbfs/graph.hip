@@ -4,8 +4,10 @@
 // Block b = i * P + j holds, for every source u in R_j (row u - j*R), its
 // neighbours v in R_i as local ids v - i*R. Tuple {u, v} contributes u -> v
 // to block (owner(v), owner(u)) and v -> u to block (owner(u), owner(v)); a
-// self-loop contributes twice to one row. Rows are built by a counting pass,
-// a per-block scan (tile sums, scan of tile sums, local scans) and a scatter.
+// self-loop contributes twice to one row. Rows are built by sorting the
+// entries (radix.hip) or, for few or very many of them, by a counting pass and
+// a scatter whose rows are sorted afterwards (sort.hip); row offsets come from
+// a per-block scan (tile sums, scan of tile sums, local scans).
 #include <vector>
 
 #include "device.hpp"
@@ -60,14 +62,20 @@ __global__ void k_count(const int64_t *src, const int64_t *dst, int64_t m, int64
     }
 }
 
+// A row's entries: cnt[row], less row_start[row] where that is given (cnt is
+// then the place after its last entry; places are below 2^32).
+__device__ __forceinline__ int32_t row_count(const int32_t *cnt, const int32_t *row_start, int64_t row) {
+    return (int32_t)((uint32_t)cnt[row] - (row_start ? (uint32_t)row_start[row] : 0u));
+}
+
 // tile sums of every block's row counts: sums[b * ntile + t]
-__global__ __launch_bounds__(kThreads) void k_tile_sum(const int32_t *cnt, int64_t R, int64_t ntile,
-                                                       long long *sums) {
+__global__ __launch_bounds__(kThreads) void k_tile_sum(const int32_t *cnt, const int32_t *row_start, int64_t R,
+                                                       int64_t ntile, long long *sums) {
     const int64_t t = blockIdx.x, b = blockIdx.y;
     long long s = 0;
     for (int64_t k = threadIdx.x; k < kTile; k += kThreads) {
         const int64_t u = t * kTile + k;
-        if (u < R) s += cnt[b * R + u];
+        if (u < R) s += row_count(cnt, row_start, b * R + u);
     }
     __shared__ long long red[kThreads / 64];
     for (int d = 32; d > 0; d >>= 1) s += __shfl_xor(s, d, 64);
@@ -98,7 +106,7 @@ __global__ __launch_bounds__(kThreads) void k_tile_scan(long long *sums, int64_t
 
 // row_ptr[b * (R + 1) + u] = exclusive prefix of row counts within block b;
 // the counts become the scatter cursors (cursor[u] = row_ptr[u]).
-__global__ __launch_bounds__(kThreads) void k_tile_apply(int32_t *cnt, int64_t R, int64_t ntile,
+__global__ __launch_bounds__(kThreads) void k_tile_apply(int32_t *cnt, const int32_t *row_start, int64_t R, int64_t ntile,
                                                          const long long *sums, int32_t *row_ptr) {
     const int64_t t = blockIdx.x, b = blockIdx.y;
     const int64_t u0 = t * kTile + threadIdx.x * kTileItems;
@@ -106,7 +114,7 @@ __global__ __launch_bounds__(kThreads) void k_tile_apply(int32_t *cnt, int64_t R
     long long mine = 0;
     for (int k = 0; k < kTileItems; ++k) {
         const int64_t u = u0 + k;
-        v[k] = u < R ? cnt[b * R + u] : 0;
+        v[k] = u < R ? row_count(cnt, row_start, b * R + u) : 0;
         mine += v[k];
     }
     long long tot;
@@ -328,6 +336,12 @@ __global__ void k_live(const int32_t *deg, int64_t n, uint64_t *live) {
     if ((threadIdx.x & 63) == 0 && v < n) live[v >> 6] = b;
 }
 
+// Builds of this many entries sort them (radix.hip) instead of counting,
+// scattering and sorting rows. R-MAT, 4 x 4, in us (sort, else): 2^17 entries
+// 313, 321; 2^18 324, 412; 2^20 342, 533; 2^25 1820, 5850; 2^31 (8 x 8) 145 ms,
+// 397. Above, the places do not fit 32 bits.
+constexpr int64_t kSortMin = int64_t(1) << 18, kSortMax = int64_t(1) << 31;
+
 constexpr int kMiscWords = 64;  // build flags and counters: err, sort queue counts, check, big items
 
 int check_sizes(int64_t n, int64_t n_tuples, int32_t p, const char *who) {
@@ -361,16 +375,19 @@ int graph_layout(int64_t n, int64_t n_tuples, int32_t p, GraphLayout *L) {
     g.row_ptr = take(4 * g.B * (g.R + 1));
     g.col_base = take(8 * (g.B + 1));
     g.col = take(4 * g.nnz);
+    g.pull_col = take(4 * g.nnz);  // right after col: together they hold 8 bytes an entry for the build's sort
     g.dir = take(8 * g.B * g.W);
     g.deg = take(4 * n);
     g.pull_off = take(8 * (n + 1));
-    g.pull_col = take(4 * g.nnz);
     g.head = take(8 * n);
     g.live = take(8 * (n / 64));
     g.qoff = take(8 * (g.P + 1));
     g.small = take(8 * 64);
     g.graph_bytes = o;
     o = 0;
+    g.sorted = g.nnz >= kSortMin && g.nnz <= kSortMax;
+    g.radix = g.sorted ? take(radix_scratch_bytes(g.nnz)) : 0;
+    g.row_start = g.sorted ? take(4 * g.B * g.R) : 0;
     g.cnt = take(4 * g.B * g.R);
     g.sums = take(8 * g.B * g.ntile);
     g.nnzb = take(8 * g.B);
@@ -440,24 +457,28 @@ extern "C" int csbfs_graph_build_into(const int64_t *src, const int64_t *dst, in
 
     CSBFS_HIP(hipMemsetAsync(cnt, 0, sizeof(int32_t) * B * R, st));
     CSBFS_HIP(hipMemsetAsync(misc, 0, sizeof(unsigned long long) * (kMiscWords + p), st));
-    if (n_tuples > 0) {
+    int32_t *row_start = nullptr;
+    if (L.sorted) {
+        row_start = (int32_t *)(sm + L.row_start);
+        CSBFS_HIP(hipMemsetAsync(row_start, 0, sizeof(int32_t) * B * R, st));
+        rc = sort_entries(src, dst, n_tuples, n, p, sm + L.radix, g->col, g->col, row_start, cnt, err, st);
+        if (rc) return rc;
+    } else if (n_tuples > 0) {
         hipLaunchKernelGGL(k_count, dim3(grid_for(n_tuples, kThreads, 65536)), dim3(kThreads), 0, st, src,
                            dst, n_tuples, n, R, p, cnt, err);
         CSBFS_HIP(hipGetLastError());
     }
     int32_t herr = 0;
     CSBFS_HIP(hipMemcpyAsync(&herr, err, sizeof(herr), hipMemcpyDeviceToHost, st));
-    CSBFS_HIP(hipStreamSynchronize(st));
-    if (herr) return fail(CSBFS_ERANGE, "csbfs_graph_build_into: a tuple id is outside [0, n)");
-
     hipLaunchKernelGGL(k_tile_sum, dim3((unsigned)ntile, (unsigned)B), dim3(kThreads), 0, st,
-                       (const int32_t *)cnt, R, ntile, sums);
+                       (const int32_t *)cnt, (const int32_t *)row_start, R, ntile, sums);
     CSBFS_HIP(hipGetLastError());
     hipLaunchKernelGGL(k_tile_scan, dim3((unsigned)B), dim3(kThreads), 0, st, sums, ntile, nnzb);
     CSBFS_HIP(hipGetLastError());
     std::vector<long long> nnz(B);
     CSBFS_HIP(hipMemcpyAsync(nnz.data(), nnzb, sizeof(long long) * B, hipMemcpyDeviceToHost, st));
     CSBFS_HIP(hipStreamSynchronize(st));
+    if (herr) return fail(CSBFS_ERANGE, "csbfs_graph_build_into: a tuple id is outside [0, n)");
     std::vector<int64_t> base(B + 1, 0);
     int64_t maxb = 0;
     for (int64_t b = 0; b < B; ++b) {
@@ -469,18 +490,18 @@ extern "C" int csbfs_graph_build_into(const int64_t *src, const int64_t *dst, in
     const int64_t total = base[B];
     if (total != L.nnz) return fail(CSBFS_ECORRUPT, "csbfs_graph_build_into: adjacency count mismatch");
     CSBFS_HIP(hipMemcpyAsync(g->col_base, base.data(), sizeof(int64_t) * (B + 1), hipMemcpyHostToDevice, st));
-    hipLaunchKernelGGL(k_tile_apply, dim3((unsigned)ntile, (unsigned)B), dim3(kThreads), 0, st, cnt, R,
-                       ntile, (const long long *)sums, g->row_ptr);
+    hipLaunchKernelGGL(k_tile_apply, dim3((unsigned)ntile, (unsigned)B), dim3(kThreads), 0, st, cnt,
+                       (const int32_t *)row_start, R, ntile, (const long long *)sums, g->row_ptr);
     CSBFS_HIP(hipGetLastError());
-    if (n_tuples > 0) {
+    if (n_tuples > 0 && !L.sorted) {
         hipLaunchKernelGGL(k_scatter, dim3(grid_for(n_tuples, kThreads, 65536)), dim3(kThreads), 0, st,
                            src, dst, n_tuples, R, p, cnt, (const int64_t *)g->col_base, g->col);
         CSBFS_HIP(hipGetLastError());
     }
-    // rows in decreasing id order; pull_col serves as the sort's temp buffer
-    // (it is filled from the sorted blocks afterwards)
-    rc = sort_rows_desc(g->col, g->pull_col, g->row_ptr, g->col_base, R, p, total,
-                        (int64_t *)(sm + L.queues), qcount, err, st);
+    // rows in decreasing id order, if they are not yet (pull_col serves as the
+    // row sort's temp buffer; it is filled from the sorted blocks afterwards)
+    rc = sort_rows_desc(g->col, g->pull_col, g->row_ptr, g->col_base, R, p, total, (int64_t *)(sm + L.queues), qcount,
+                        err, L.sorted, st);
     if (rc) return rc;
     hipLaunchKernelGGL(k_directory, dim3(grid_for(B * W * 64, kThreads, 65536)), dim3(kThreads), 0, st,
                        (const int32_t *)g->row_ptr, R, W, B, g->dir);
@@ -546,18 +567,20 @@ extern "C" int csbfs_graph_build(const int64_t *src, const int64_t *dst, int64_t
     GraphLayout L;
     int rc = graph_layout(n, n_tuples, p, &L);
     if (rc) return rc;
-    void *gm = nullptr, *sm = nullptr;
-    CSBFS_HIP(hipMalloc(&gm, (size_t)L.graph_bytes));
-    hipError_t e = hipMalloc(&sm, (size_t)L.scratch_bytes);
-    if (e != hipSuccess) {
-        (void)hipFree(gm);
-        return hip_fail(e, "hipMalloc(build scratch)", __FILE__, __LINE__);
-    }
-    rc = csbfs_graph_build_into(src, dst, n_tuples, n, p, gm, (size_t)L.graph_bytes, sm,
-                                (size_t)L.scratch_bytes, stream, out);
-    (void)hipFree(sm);
+    DeviceBlock gm, sm;
+    rc = device_take((size_t)L.graph_bytes, &gm);
+    if (rc) return rc;
+    rc = device_take((size_t)L.scratch_bytes, &sm);
     if (rc) {
-        (void)hipFree(gm);
+        device_give(gm);
+        return rc;
+    }
+    rc = csbfs_graph_build_into(src, dst, n_tuples, n, p, gm.p, gm.bytes, sm.p, sm.bytes, stream, out);
+    // a failed build may have left work behind that still uses the blocks
+    if (rc) (void)hipStreamSynchronize(as_stream(stream));
+    device_give(sm);
+    if (rc) {
+        device_give(gm);
         return rc;
     }
     (*out)->owned = gm;
@@ -566,9 +589,9 @@ extern "C" int csbfs_graph_build(const int64_t *src, const int64_t *dst, int64_t
 
 extern "C" int csbfs_graph_free(csbfs_graph *g) {
     if (!g) return CSBFS_OK;
-    // a caller-owned buffer stays the caller's; hipFree orders itself after
-    // the device work that may still use the library's own buffer
-    if (g->owned) (void)hipFree(g->owned);
+    // a caller-owned buffer stays the caller's; the library's own is let go
+    // once the device work that may still use it is done
+    if (g->owned.p) device_release(g->device, g->owned);
     delete g;
     return CSBFS_OK;
 }

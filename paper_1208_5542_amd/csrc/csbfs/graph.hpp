@@ -32,7 +32,8 @@ struct GraphLayout {
     // graph buffer
     int64_t row_ptr, col_base, col, dir, deg, pull_off, pull_col, head, live, qoff, small, graph_bytes;
     // build scratch
-    int64_t cnt, sums, nnzb, misc, queues, scan, scratch_bytes;
+    bool sorted;  // entries sorted as a whole (radix.hip)
+    int64_t radix, row_start, cnt, sums, nnzb, misc, queues, scan, scratch_bytes;
 };
 int graph_layout(int64_t n, int64_t n_tuples, int32_t p, GraphLayout *out);
 
@@ -49,7 +50,7 @@ struct csbfs_graph {
     int64_t max_block_nnz = 0;
     std::vector<int64_t> big_items;  // per block-row: queue items if every row were expanded at once
     int64_t device_bytes = 0;
-    void *owned = nullptr;            // the graph buffer when the library allocated it
+    csbfs::DeviceBlock owned;         // the graph buffer when the library allocated it
     // block b = i * P + j: rows are sources u in R_j, columns targets in R_i
     int32_t *row_ptr = nullptr;       // [P*P][R + 1], offsets within the block
     int64_t *col_base = nullptr;      // [P*P + 1], block start in col
@@ -70,7 +71,8 @@ struct csbfs_graph {
 
 namespace csbfs {
 int graph_device_check(const csbfs_graph *g);
-// Sort every block row (descending target id) in place; tmp has nnz entries
+// Sort every block row (descending target id) in place, unless `sorted` says
+// it is (the long rows are then only queued); tmp has nnz entries
 // of scratch, queues and q_count come from the build scratch.
 // Rows above kLongRow entries are sorted (and copied into the pull layout) by
 // whole workgroups; the sort leaves their numbers b * R + u in two queues.
@@ -84,7 +86,14 @@ int64_t sort_queue_cap(int64_t nnz, int which);
 LongRows sort_long_rows(const int64_t *queues, const unsigned long long *q_count, int64_t nnz);
 int sort_rows_desc(uint32_t *col, uint32_t *tmp, const int32_t *row_ptr, const int64_t *col_base, int64_t R,
                    int32_t P, int64_t nnz, int64_t *queues, unsigned long long *q_count, int32_t *err,
-                   hipStream_t st);
+                   bool sorted, hipStream_t st);
+// Every entry of the tuples to its sorted place in col (all blocks, rows in
+// decreasing id order), and each non-empty row's first and last place + 1;
+// *err is set by a tuple id outside [0, n). `keys` holds 8 bytes an entry and
+// may overlap col.
+int64_t radix_scratch_bytes(int64_t nnz);
+int sort_entries(const int64_t *src, const int64_t *dst, int64_t n_tuples, int64_t n, int32_t P, void *scratch,
+                 void *keys, uint32_t *col, int32_t *row_start, int32_t *row_end, int32_t *err, hipStream_t st);
 // off[v] = sum of deg[u] for u < v (off has n + 1 entries; off[n] = total);
 // tile_sum holds scan_tiles(n) entries of scratch.
 int64_t scan_tiles(int64_t n);

@@ -214,7 +214,13 @@ void worker(csbfs_server *s, int slot) {
             void *mem = nullptr;
             csbfs_batch_engine *eng = nullptr;
             int rc = CSBFS_OK;
-            if (hipMallocAsync(&mem, (size_t)need, st) != hipSuccess) {
+            hipError_t me = hipMallocAsync(&mem, (size_t)need, st);
+            if (me == hipErrorOutOfMemory) {
+                (void)hipGetLastError();
+                device_trim();
+                me = hipMallocAsync(&mem, (size_t)need, st);
+            }
+            if (me != hipSuccess) {
                 (void)hipGetLastError();
                 rc = CSBFS_EHIP;
                 mem = nullptr;

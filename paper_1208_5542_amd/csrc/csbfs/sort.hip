@@ -133,6 +133,44 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_short(SortArgs a) {
     }
 }
 
+// Rows already in order: only the long ones' numbers are wanted. A workgroup
+// collects those of kQueueRows rows in LDS and reserves their slots at once
+// (per wave, the atomics on the two counters were most of 63 us at scale 20).
+constexpr int kQueueRows = 4096;
+__global__ __launch_bounds__(kSortThreads) void k_queue_long(SortArgs a) {
+    __shared__ uint16_t found[2][kQueueRows];
+    __shared__ uint32_t count[2];
+    __shared__ unsigned long long base[2];
+    if (threadIdx.x < 2) count[threadIdx.x] = 0;
+    __syncthreads();
+    const int64_t row0 = (int64_t)blockIdx.x * kQueueRows;
+    for (int k = threadIdx.x; k < kQueueRows; k += kSortThreads) {
+        if (row0 + k >= a.rows) break;
+        // row r of block b is entry r + b of the row offsets
+        const int32_t *rp = a.row_ptr + row0 + k + (uint64_t)(row0 + k) / (uint64_t)a.R;
+        const int32_t len = rp[1] - rp[0];
+        if (len > kWaveRow) {
+            const int c = len > kBlockRow;
+            found[c][atomicAdd(&count[c], 1u)] = (uint16_t)k;
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x < 2 && count[threadIdx.x])
+        base[threadIdx.x] = atomicAdd(&a.q_count[1 + threadIdx.x], (unsigned long long)count[threadIdx.x]);
+    __syncthreads();
+    for (int c = 0; c < 2; ++c) {
+        int64_t *q = c ? a.q_radix : a.q_block;
+        const int64_t cap = c ? a.cap_radix : a.cap_block;
+        for (uint32_t k = threadIdx.x; k < count[c]; k += kSortThreads) {
+            const int64_t pos = (int64_t)base[c] + k;
+            if (pos < cap)
+                q[pos] = row0 + found[c][k];
+            else
+                *a.err = 1;  // cannot happen: capacities bound the row counts
+        }
+    }
+}
+
 // Bitonic network over m (a power of two) slots of LDS, descending; `sync`
 // orders the stages (wave or workgroup).
 template <class Sync>
@@ -396,7 +434,7 @@ int64_t scan_tiles(int64_t n) { return (n + kScanTile - 1) / kScanTile; }
 
 int sort_rows_desc(uint32_t *col, uint32_t *tmp, const int32_t *row_ptr, const int64_t *col_base, int64_t R,
                    int32_t P, int64_t nnz, int64_t *queues, unsigned long long *q_count, int32_t *err,
-                   hipStream_t st) {
+                   bool sorted, hipStream_t st) {
     if (nnz == 0) return CSBFS_OK;
     SortArgs a{};
     a.col = col;
@@ -417,6 +455,11 @@ int sort_rows_desc(uint32_t *col, uint32_t *tmp, const int32_t *row_ptr, const i
     a.key_bits = bits;
     a.err = err;
     CSBFS_HIP(hipMemsetAsync(q_count, 0, 3 * sizeof(unsigned long long), st));
+    if (sorted) {
+        hipLaunchKernelGGL(k_queue_long, dim3((unsigned)((a.rows + kQueueRows - 1) / kQueueRows)), dim3(kSortThreads), 0, st, a);
+        CSBFS_HIP(hipGetLastError());
+        return CSBFS_OK;
+    }
     hipLaunchKernelGGL(k_sort_short, dim3(grid_for(a.rows, kSortThreads, 65536)), dim3(kSortThreads), 0, st, a);
     CSBFS_HIP(hipGetLastError());
     hipLaunchKernelGGL(k_sort_wave, dim3(4096), dim3(kSortThreads), 0, st, a);
