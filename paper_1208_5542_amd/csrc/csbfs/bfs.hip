@@ -59,8 +59,8 @@ constexpr int kEvPerLevel = 5;  // before/after the update + encode, after the d
 constexpr int kPullTileDense = 64;  // bitmap words per wave tile of the dense pull
 constexpr int kPullTileBU = 8;      // ... and of the bottom-up pull (many more candidates; 8 beat 2 and 4)
 constexpr int32_t kDirTD = CSBFS_DIR_TOP_DOWN, kDirBU = CSBFS_DIR_BOTTOM_UP, kDirDense = CSBFS_DIR_DENSE;
-// No frontier left: every kernel of the iteration returns at once (the
-// host learns of it one iteration late, and that iteration costs nothing).
+// No frontier left: the expansion kernels queued behind the reduction that
+// found it return at once.
 constexpr int32_t kDirIdle = 3;
 
 // One chunk of a long row: its entries col[gcol, gcol + len) are the
@@ -178,7 +178,7 @@ constexpr int kBigUnroll = 2;   // edges in flight per lane in the long-row kern
 //   sparse: an unvisited v takes u by atomicMax into parent[v]; the lane
 //           that finds it still without a parent also sets its N bit.
 //   dense:  an unvisited v is only marked in N.
-template <bool kDense, int U>
+template <bool kDense, int U, bool kEager = false>
 __device__ __forceinline__ void relax_batch(const ExpandArgs &a, const int64_t (&v)[U], const int32_t (&u)[U],
                                             const bool (&ok)[U]) {
     if (kDense) {
@@ -201,11 +201,20 @@ __device__ __forceinline__ void relax_batch(const ExpandArgs &a, const int64_t (
 #pragma unroll
         for (int k = 0; k < U; ++k) pw[k] = ok[k] ? a.pi[v[k] >> 6] : ~0ull;
         int32_t old[U];
+        if constexpr (kEager) {
+#pragma unroll
+            for (int k = 0; k < U; ++k)
+                old[k] = ok[k] ? __hip_atomic_load(&a.parent[v[k]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                               : INT32_MAX;
+        }
 #pragma unroll
         for (int k = 0; k < U; ++k) {
             const bool need = !((pw[k] >> (v[k] & 63)) & 1);
-            old[k] = need ? __hip_atomic_load(&a.parent[v[k]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
-                          : INT32_MAX;
+            if (kEager)
+                old[k] = need ? old[k] : INT32_MAX;
+            else
+                old[k] = need ? __hip_atomic_load(&a.parent[v[k]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                              : INT32_MAX;
         }
         // The first atomicMax on a vertex comes from a lane whose load still
         // saw no parent: that lane also sets its N bit, so N is exactly this
@@ -228,14 +237,15 @@ __device__ __forceinline__ void relax_batch(const ExpandArgs &a, const int64_t (
 // the lanes, kUnroll edges per lane per step.
 // The view word of this lane in tile `tile` of processor r (0 past the end,
 // and 0 without a load where the frontier's block mark is clear).
+template <bool kEager>
 __device__ __forceinline__ uint64_t tile_word(const ExpandArgs &a, int32_t r, int64_t tile) {
     const int lane = threadIdx.x & 63;
     const int64_t wl = tile * a.tile_words + lane;
-    const bool in = lane < a.tile_words && wl < a.rank_words && a.marks_view.word_marked(wl);
+    const bool in = lane < a.tile_words && wl < a.rank_words && (kEager || a.marks_view.word_marked(wl));
     return in ? a.view[(int64_t)r * a.rank_words + wl] : 0;
 }
 
-template <bool kDense>
+template <bool kDense, bool kEager>
 __device__ __forceinline__ void expand_tile(const ExpandArgs &a, int32_t r, int64_t tile, uint64_t bits,
                                             unsigned long long &edges) {
     const int lane = threadIdx.x & 63;
@@ -314,7 +324,7 @@ __device__ __forceinline__ void expand_tile(const ExpandArgs &a, int32_t r, int6
             }
 #pragma unroll
             for (int k = 0; k < kUnroll; ++k) v[k] = vbase + c[k];
-            relax_batch<kDense, kUnroll>(a, v, uu, ok);
+            relax_batch<kDense, kUnroll, kEager>(a, v, uu, ok);
         }
     }
 }
@@ -324,7 +334,7 @@ __device__ __forceinline__ void expand_tile(const ExpandArgs &a, int32_t r, int6
 // (lane = source u). Rows longer than kBigRow go to the processor's chunk
 // queue (one wave-aggregated reservation); the remaining edges of the 64
 // sources are spread evenly over the lanes, kUnroll edges per lane per step.
-template <bool kDense>
+template <bool kDense, bool kEager = false>
 __device__ __forceinline__ void expand_body(const ExpandArgs &a) {
     const int lane = threadIdx.x & 63;
     const int64_t wave = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
@@ -343,7 +353,7 @@ __device__ __forceinline__ void expand_body(const ExpandArgs &a) {
         if (mine < total) {
             const uint32_t r = (uint32_t)mine / (uint32_t)ntiles;
             const int64_t t = mine - (int64_t)r * ntiles;
-            marked = a.marks_view.m[(t * a.tile_words) >> kMarkShift] != 0;
+            marked = kEager || a.marks_view.m[(t * a.tile_words) >> kMarkShift] != 0;
         }
         uint64_t todo = __ballot(marked);
         while (todo) {
@@ -362,12 +372,12 @@ __device__ __forceinline__ void expand_body(const ExpandArgs &a) {
                     const uint32_t r = (uint32_t)gt / (uint32_t)ntiles;
                     rs[k] = (int32_t)r;
                     ts[k] = gt - (int64_t)r * ntiles;
-                    bits[k] = tile_word(a, (int32_t)r, ts[k]);
+                    bits[k] = tile_word<kEager>(a, (int32_t)r, ts[k]);
                 }
             }
 #pragma unroll
             for (int k = 0; k < kTilesAhead; ++k)
-                if (rs[k] >= 0 && __ballot(bits[k] != 0)) expand_tile<kDense>(a, rs[k], ts[k], bits[k], edges);
+                if (rs[k] >= 0 && __ballot(bits[k] != 0)) expand_tile<kDense, kEager>(a, rs[k], ts[k], bits[k], edges);
         }
     }
     // `total` is wave-uniform, so every lane holds the wave's edge count
@@ -823,17 +833,29 @@ __global__ __launch_bounds__(kPullThreads) void pull_kernel(PullArgs a) {
 // One launch per level for the default (direction-optimizing) search: the
 // top-down push or the bottom-up pull, as the level's direction says.
 static_assert(kExpThreads == kPullThreads, "one block size for both directions");
+template <bool kEager>
 __device__ __forceinline__ void level_body(ExpandArgs ea, const PullArgs &pa) {
     const int32_t d = *ea.dir;
     if (d == kDirBU) {
         pull_body<true>(pa);
     } else if (d != kDirIdle) {
         ea.tile_words = *ea.tile;
-        expand_body<false>(ea);
+        expand_body<false, kEager>(ea);
     }
 }
 
-__global__ __launch_bounds__(kExpThreads) void level_kernel(ExpandArgs ea, PullArgs pa) { level_body(ea, pa); }
+__global__ __launch_bounds__(kExpThreads) void level_kernel(ExpandArgs ea, PullArgs pa) { level_body<false>(ea, pa); }
+
+// Graphs of kEagerWords bitmap words or fewer: a level is a chain of round
+// trips to memory with little in flight, so what the larger graphs load only
+// if an earlier load says so (view words behind block marks, parents behind
+// visited bits, the encoder's words and marks) is loaded at once. Scale 16, 4 x
+// 4: 216.6 -> 213.7 us a search; 393k vertices, p 3: 308.5 -> 303.3; scale 20
+// Erdos-Renyi 365.0 -> 355.2; scale 22 433.1 -> 427.9.
+constexpr int64_t kEagerWords = int64_t(1) << 16;
+__global__ __launch_bounds__(kExpThreads) void level_kernel_eager(ExpandArgs ea, PullArgs pa) {
+    level_body<true>(ea, pa);
+}
 
 // The same for large graphs (kWideWords bitmap words or more): a register
 // budget of 80 (6 waves per SIMD, at the price of a few spills) so that three
@@ -845,7 +867,7 @@ constexpr int64_t kWideWords = int64_t(1) << 18;  // n >= 2^24
 constexpr unsigned kWideGrid = 768;
 __global__ __launch_bounds__(kExpThreads) __attribute__((amdgpu_waves_per_eu(6))) void level_kernel_wide(
     ExpandArgs ea, PullArgs pa) {
-    level_body(ea, pa);
+    level_body<false>(ea, pa);
 }
 
 // Binned push, second half: bin b takes the highest source of each target
@@ -995,8 +1017,7 @@ struct DirArgs {
 // m_f = entries of the new frontier, m_u = entries of unvisited vertices.
 // Top-down turns bottom-up when m_f * alpha > m_u; bottom-up turns top-down
 // when the frontier is below n / beta and shrinking. One thread.
-__device__ void choose_direction(const DirArgs &a, unsigned long long nf, unsigned long long mf) {
-    DirState s = *a.st;
+__device__ void choose_direction(const DirArgs &a, DirState s, unsigned long long nf, unsigned long long mf) {
     s.vdeg += mf;
     const double mu = (double)a.nnz - (double)s.vdeg;
     int32_t next = s.cur;
@@ -1054,6 +1075,7 @@ __device__ __forceinline__ unsigned long long *update_sums() {
 // vertex; all masked loads of a step in flight before any is summed). Each word is taken by one lane, and no workgroup
 // of this launch reads pi or N_old, so the plain read-modify-writes need no
 // atomics.
+template <bool kEager>
 struct FrontierHook {
     const uint64_t *N_cur;   // f^k: vertices discovered while expanding f^(k-1)
     uint64_t *N_old;         // f^(k-1): cleared here, refilled by the next expansion
@@ -1080,6 +1102,7 @@ struct FrontierHook {
     }
     // the whole workgroup: is every block of sender i's segment unmarked?
     __device__ __forceinline__ bool clean(const WahBatch &b, int64_t seg, const StreamIdx &x) const {
+        if (kEager) return false;
         const int64_t g0 = x.i * W + seg * seg_words, g1 = x.i * W + seg_end(b, seg);
         const int64_t k0 = g0 >> kMarkShift, k1 = (g1 - 1) >> kMarkShift;
         int any = 0;
@@ -1103,7 +1126,10 @@ struct FrontierHook {
         const int64_t q0 = seg * seg_words;
         const int64_t q1 = seg_end(b, seg);
         const int64_t base = x.i * W;
-        if (clear_views) {
+        if (kEager && clear_views) {
+            uint64_t *vw = view + (x.j * P + x.i) * W;
+            for (int64_t q = q0 + t; q < q1; q += nt) vw[q] = 0;
+        } else if (clear_views) {
             // one 64-word block per wave at a time (lane = word); the marks of
             // 64 of the wave's blocks are loaded at once first
             uint64_t *vw = view + (x.j * P + x.i) * W;
@@ -1130,7 +1156,13 @@ struct FrontierHook {
             const int64_t c = cb + (int64_t)(lane / kUpdWords) * wstride;
             const int64_t qk = q0 + c * kUpdWords + (lane % kUpdWords);
             uint64_t tk = 0;
-            if (c < nsteps && qk < q1) {
+            if (kEager && c < nsteps && qk < q1) {
+                tk = N_cur[base + qk];
+                const uint64_t seen = pi[base + qk], old = N_old[base + qk];
+                if (tk) pi[base + qk] = seen | tk;
+                if (old) N_old[base + qk] = 0;
+                cnt += (unsigned long long)__popcll(tk);
+            } else if (c < nsteps && qk < q1) {
                 if (mark_cur.word_marked(base + qk)) {
                     tk = N_cur[base + qk];
                     if (tk) pi[base + qk] |= tk;
@@ -1182,12 +1214,11 @@ struct FrontierHook {
 };
 
 // Update + sieve + compress of level k (k >= 1): one workgroup per (stream,
-// segment). Returns at once once the search has ended.
-template <int kGpt>
-__device__ __forceinline__ void frontier_encode_body(const WahBatch &b, FrontierHook &h, const DirState *st,
+// segment).
+template <int kGpt, bool kEager>
+__device__ __forceinline__ void frontier_encode_body(const WahBatch &b, FrontierHook<kEager> &h, const DirState *st,
                                                      int32_t split) {
     const int32_t d = st->cur;  // the direction f^(k-1) was expanded in
-    if (d == kDirIdle) return;
     h.clear_views = d != kDirTD;  // the sparse push zeroes the view words it reads
     h.write_levels = d == kDirTD;  // a pull wrote the levels of the vertices it found
     int64_t s;
@@ -1198,9 +1229,10 @@ __device__ __forceinline__ void frontier_encode_body(const WahBatch &b, Frontier
 
 // Segments of 1024 groups: the grids of smaller graphs (fewer workgroups than
 // the GPU holds), where the register budget below only costs spills.
-__global__ __launch_bounds__(kEncThreads) void frontier_encode_kernel_g2(WahBatch b, FrontierHook h,
+template <bool kEager>
+__global__ __launch_bounds__(kEncThreads) void frontier_encode_kernel_g2(WahBatch b, FrontierHook<kEager> h,
                                                                       const DirState *st, int32_t split) {
-    frontier_encode_body<2>(b, h, st, split);
+    frontier_encode_body<2, kEager>(b, h, st, split);
 }
 
 // Segments of 2048 groups, for large graphs: 8 waves per SIMD (the 106
@@ -1209,8 +1241,8 @@ __global__ __launch_bounds__(kEncThreads) void frontier_encode_kernel_g2(WahBatc
 // fitting. Scale 26, 16 roots: encoder 0.532 -> 0.497 ms per search, 367.6
 // -> 373.1 GTEPS.
 __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(8))) void frontier_encode_kernel_g4(
-    WahBatch b, FrontierHook h, const DirState *st, int32_t split) {
-    frontier_encode_body<4>(b, h, st, split);
+    WahBatch b, FrontierHook<false> h, const DirState *st, int32_t split) {
+    frontier_encode_body<4, false>(b, h, st, split);
 }
 
 struct ReduceArgs {
@@ -1229,12 +1261,11 @@ struct ReduceArgs {
 
 // Decode of level k into the views; workgroup (0, 0) first reduces the
 // update's sums, stores the level's counters, writes |f^k| for the host and
-// chooses the direction of the expansion of f^k. A workgroup that starts
-// after that choice and finds the idle direction has an empty frontier's
-// streams to decode, which set no bit: returning is the same.
+// chooses the direction of the expansion of f^k (no other workgroup reads it).
 __global__ __launch_bounds__(kDecThreads) __attribute__((amdgpu_waves_per_eu(6))) void search_decode_kernel(WahBatch b, ReduceArgs r) {
-    if (r.dir.st->cur == kDirIdle) return;
     if (blockIdx.x == 0 && blockIdx.y == 0) {
+        const DirState state = *r.dir.st;  // loaded beside the sums
+        const unsigned long long pulled = *r.exp_mf;
         unsigned long long nf = 0, mf = 0;
         for (int64_t k = threadIdx.x; k < r.nparts; k += blockDim.x) {
             nf += r.part[2 * k];
@@ -1245,7 +1276,7 @@ __global__ __launch_bounds__(kDecThreads) __attribute__((amdgpu_waves_per_eu(6))
         if (threadIdx.x < r.P) r.ctrs[threadIdx.x] = 0;
         for (int64_t k = threadIdx.x; k < r.nmarks; k += blockDim.x) r.marks_clear[k] = 0;
         if (threadIdx.x == 0) {
-            mf += *r.exp_mf;  // f^k came from a pull: its entries were summed there
+            mf += pulled;  // f^k came from a pull: its entries were summed there
             *r.exp_mf = 0;
             r.total[0] = nf;
             r.total[1] = mf;
@@ -1253,7 +1284,7 @@ __global__ __launch_bounds__(kDecThreads) __attribute__((amdgpu_waves_per_eu(6))
             if (r.host)
                 __hip_atomic_store(r.host, ((unsigned long long)r.level << 32) | nf, __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_SYSTEM);
-            choose_direction(r.dir, nf, mf);
+            choose_direction(r.dir, state, nf, mf);
         }
     }
     // the grid holds at most kDecGridChunks workgroups per stream, each
@@ -1788,7 +1819,7 @@ int run_search(const csbfs_graph *g, const SearchLayout &y, const SearchState &w
     // which beat 512-4096; 768 for the wide level kernel) and kBinGrid for
     // the long rows
     const unsigned exp_grid = 512, big_grid = kBinGrid;
-    const bool wide = words >= kWideWords;
+    const bool wide = words >= kWideWords, eager = words <= kEagerWords;
     const unsigned level_grid = wide ? kWideGrid : exp_grid;
     const unsigned pull_grid = grid_for((words + kPullTileDense - 1) / kPullTileDense, kPullThreads / 64, 16384);
     const unsigned bu_grid = grid_for((words + kPullTileBU - 1) / kPullTileBU, kPullThreads / 64, 2048);
@@ -1834,14 +1865,19 @@ int run_search(const csbfs_graph *g, const SearchLayout &y, const SearchState &w
             wb.n_words = w.lc.words(sj);
             wb.stat_sieved_bits = w.lc.sbits(sj);
             wb.stat_unsieved_words = w.lc.uwords(sj);
-            FrontierHook fh{w.nb[j & 1], w.nb[(j + 1) & 1], w.pi, w.view, level, g->deg, w.part,
-                            marks_of(j), marks_of(j + 1), W, y.seg_words, (int32_t)P, (int32_t)j, 1, 1};
-            if (y.enc_gpt == 2)
-                hipLaunchKernelGGL(frontier_encode_kernel_g2, enc_grid, dim3(kEncThreads), 0, st, wb, fh,
-                                   (const DirState *)w.dstate, enc_split);
+            auto hook = [&](auto h) {
+                return decltype(h){w.nb[j & 1], w.nb[(j + 1) & 1], w.pi, w.view, level, g->deg, w.part,
+                                   marks_of(j), marks_of(j + 1), W, y.seg_words, (int32_t)P, (int32_t)j, 1, 1};
+            };
+            if (y.enc_gpt == 4)
+                hipLaunchKernelGGL(frontier_encode_kernel_g4, enc_grid, dim3(kEncThreads), 0, st, wb,
+                                   hook(FrontierHook<false>{}), (const DirState *)w.dstate, enc_split);
+            else if (eager)
+                hipLaunchKernelGGL(frontier_encode_kernel_g2<true>, enc_grid, dim3(kEncThreads), 0, st, wb,
+                                   hook(FrontierHook<true>{}), (const DirState *)w.dstate, enc_split);
             else
-                hipLaunchKernelGGL(frontier_encode_kernel_g4, enc_grid, dim3(kEncThreads), 0, st, wb, fh,
-                                   (const DirState *)w.dstate, enc_split);
+                hipLaunchKernelGGL(frontier_encode_kernel_g2<false>, enc_grid, dim3(kEncThreads), 0, st, wb,
+                                   hook(FrontierHook<false>{}), (const DirState *)w.dstate, enc_split);
             CSBFS_HIP(hipGetLastError());
             if (ev) CSBFS_HIP(hipEventRecord(ev[1], st));
             // a6: the stream slots are the receive buffers; a7: decode into the
@@ -1898,7 +1934,9 @@ int run_search(const csbfs_graph *g, const SearchLayout &y, const SearchState &w
             } else {
                 // one launch: the push or the pull, as the level's direction
                 // says; the long-row pass returns at once on bottom-up levels
-                if (wide)
+                if (eager)
+                    hipLaunchKernelGGL(level_kernel_eager, dim3(level_grid), dim3(kExpThreads), 0, st, ea, pb);
+                else if (wide)
                     hipLaunchKernelGGL(level_kernel_wide, dim3(level_grid), dim3(kExpThreads), 0, st, ea, pb);
                 else
                     hipLaunchKernelGGL(level_kernel, dim3(level_grid), dim3(kExpThreads), 0, st, ea, pb);

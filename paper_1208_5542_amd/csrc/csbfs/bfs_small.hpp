@@ -501,7 +501,7 @@ __global__ __launch_bounds__(kSmallThreads) void small_search_kernel(SmallArgs a
             int32_t rec = 0;
             d.st = &sh.dir;
             d.rec = &rec;
-            choose_direction(d, nf, mf);
+            choose_direction(d, sh.dir, nf, mf);
             next[2] = (unsigned long long)(uint32_t)rec;
             sh.edges = sh.pulled = 0;
             sh.queued = 0;

@@ -93,3 +93,24 @@ def test_caller_memory_without_mailbox():
         assert (level.cpu().numpy() == adj.bfs(root)).all()
         r = eng.bfs(root)
         assert torch.equal(r.level, level) and torch.equal(r.parent, parent)
+
+
+@pytest.mark.parametrize("n,p", [(1 << 22, 2), ((1 << 22) + 128, 2)])
+def test_sizes_around_the_eager_kernels(n, p):
+    """The level kernels that load at once and those that follow block marks:
+    same levels as the oracle, same parents and messages in either direction."""
+    from paper_1208_5542_amd import csbfs
+    rng = np.random.default_rng(n)
+    used = rng.choice(n, 40000, replace=False)  # most blocks of 4096 vertices stay empty
+    used = used[(used // 4096) % 3 == 0]
+    src, dst = used[rng.integers(0, used.size, 200000)], used[rng.integers(0, used.size, 200000)]
+    g = csbfs.Graph(torch.from_numpy(src).cuda(), torch.from_numpy(dst).cuda(), n, p)
+    ref = oracle.Adjacency(n, src, dst).bfs(int(src[0]))
+    rows = []
+    for flags in (0, csbfs.FLAG_SPARSE_ONLY, csbfs.FLAG_BOTTOM_UP_ONLY):
+        eng = csbfs.Engine(g, flags=flags)
+        r = eng.bfs(int(src[0]))
+        assert (r.level.cpu().numpy() == ref).all(), flags
+        rows.append((r.parent, eng.stream_words(r.n_levels), [s["view_bits"] for s in r.stats]))
+    for parent, words, bits in rows[1:]:
+        assert torch.equal(parent, rows[0][0]) and (words == rows[0][1]).all() and bits == rows[0][2]
