@@ -68,7 +68,7 @@ __global__ __launch_bounds__(kDecThreads) void wah_decode_kernel(DecodeArgs a) {
     const int64_t c = sh_c;
     if (c == 0 && threadIdx.x == 0) dec_tail(a.words, a.nw, a.nw, a.nbits, G, r, a.dst, a.status);
     if (c * kT * kDecChunk >= a.nw - (r > 0 ? 1 : 0)) return;
-    dec_chunk<kT>(a.words, a.nw, G, r, c, a.dst, a.status, [&](long long total) -> long long {
+    dec_chunk<kT, false>(a.words, a.nw, G, r, c, a.dst, a.status, [&](long long total) -> long long {
         if (a.nchunk <= 1) return 0;
         const long long cut = G + 1;
         if (threadIdx.x < 64) {
