@@ -553,10 +553,15 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(8))
     encode_segment<kEncGpt>(b, h, blockIdx.y, blockIdx.x == 0);
 }
 
+// Where each root's levels go.
+struct BLevels {
+    int32_t *p[kMaxRoots];  // [n] each
+};
+
 struct BUpdateArgs {
     uint64_t *vn;      // [n][2]
     uint64_t *f;       // [B][n / 64] planes of the new frontier
-    int32_t *level;    // [B][n]
+    BLevels level;
     int32_t next_level;
     int32_t B;
     int64_t n;
@@ -589,6 +594,7 @@ __global__ __launch_bounds__(kBThreads) void bupdate_kernel(BUpdateArgs a) {
     const int t_st = lane % kBTile, r_st = lane / kBTile;
     const int nsteps = (a.B + kBRootsPerOp - 1) / kBRootsPerOp;
     unsigned long long mine = 0;  // lane r: new vertices of root r seen by this wave
+    const uint64_t my_level = (uint64_t)a.level.p[lane];  // lane r: where root r's levels go
     unsigned long long u_nf = 0, u_mf = 0, u_mu = 0;  // the direction rule's sums, this lane
     for (int64_t tl = wave; tl < ntiles; tl += nwaves) {
         const int64_t q0 = tl * kBTile;
@@ -618,7 +624,8 @@ __global__ __launch_bounds__(kBThreads) void bupdate_kernel(BUpdateArgs a) {
                 for (uint64_t it = wave_or64(nw); it; it &= it - 1) {
                     const int r = __ffsll((unsigned long long)it) - 1;
                     const bool mine_r = (nw >> r) & 1;
-                    if (mine_r) a.level[(int64_t)r * a.n + v] = a.next_level;
+                    int32_t *level = (int32_t *)readlane64(my_level, r);
+                    if (mine_r) level[v] = a.next_level;
                     const uint64_t bal = __ballot(mine_r);
                     if (lane == r) plane = bal;
                 }
@@ -660,8 +667,7 @@ struct BSeedArgs {
     uint64_t *fm;      // [n]
     uint64_t *view;
     int64_t view_words;  // all planes
-    int32_t *level;
-    int64_t level_words;  // n_roots * n
+    BLevels level;
     int64_t n;
     uint32_t *zero;       // counters, look-back words and tickets, queue counts, status
     int64_t zero_words;
@@ -671,18 +677,21 @@ struct BRoots {
     int64_t v[kMaxRoots];
 };
 
+// One row of workgroups per root clears its levels; all of them the rest.
 __global__ void bseed_fill_kernel(BSeedArgs a) {
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    int64_t top = a.view_words > a.level_words ? a.view_words : a.level_words;
+    const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x, row = (int64_t)gridDim.x * blockDim.x;
+    int32_t *level = a.level.p[blockIdx.y];
+    for (int64_t k = t; k < a.n; k += row) level[k] = -1;
+    const int64_t stride = row * gridDim.y;
+    int64_t top = a.view_words > a.n ? a.view_words : a.n;
     top = top > a.zero_words ? top : a.zero_words;
-    for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < top; k += stride) {
+    for (int64_t k = blockIdx.y * row + t; k < top; k += stride) {
         if (k < a.n) {
             reinterpret_cast<ulonglong2 *>(a.vn)[k] = make_ulonglong2(0ull, 0ull);
             a.fm[k] = 0;
         }
         if (k < a.zero_words) a.zero[k] = 0;
         if (k < a.view_words) a.view[k] = 0;
-        if (k < a.level_words) a.level[k] = -1;
     }
 }
 
@@ -705,7 +714,7 @@ __global__ void bseed_root_kernel(BSeedArgs a, BRoots roots, int32_t B, int64_t 
     const int64_t own = s / R, sl = s - own * R;
     atomicOr((unsigned long long *)(a.vn + 2 * s), 1ull << r);
     atomicOr((unsigned long long *)(a.fm + s), 1ull << r);
-    a.level[(int64_t)r * a.n + s] = 0;
+    a.level.p[r][s] = 0;
     for (int32_t i = 0; i < P; ++i)
         a.view[r * vplane + ((int64_t)i * P + own) * W + (sl >> 6)] = 1ull << (sl & 63);
     root_count0[r] = 1;
@@ -939,6 +948,16 @@ extern "C" int csbfs_batch_engine_free(csbfs_batch_engine *e) {
 extern "C" int csbfs_batch_bfs(csbfs_batch_engine *e, const int64_t *roots, int32_t n_roots,
                                int32_t *level, csbfs_level_stats *stats, int32_t stats_cap,
                                int32_t *n_levels, void *stream) {
+    if (!e || !level) return fail(CSBFS_EINVAL, "csbfs_batch_bfs: null argument or negative stats_cap");
+    int32_t *rows[kMaxRoots];
+    for (int32_t r = 0; r < n_roots && r < kMaxRoots; ++r) rows[r] = level + (int64_t)r * e->g->n;
+    return batch_bfs_into(e, roots, n_roots, rows, stats, stats_cap, n_levels, stream);
+}
+
+namespace csbfs {
+
+int batch_bfs_into(csbfs_batch_engine *e, const int64_t *roots, int32_t n_roots, int32_t *const *level,
+                   csbfs_level_stats *stats, int32_t stats_cap, int32_t *n_levels, void *stream) {
     if (!e || !roots || !level || !n_levels || stats_cap < 0 || (stats_cap > 0 && !stats))
         return fail(CSBFS_EINVAL, "csbfs_batch_bfs: null argument or negative stats_cap");
     if (n_roots < 1 || n_roots > e->Bmax)
@@ -957,7 +976,9 @@ extern "C" int csbfs_batch_bfs(csbfs_batch_engine *e, const int64_t *roots, int3
     // a0: seed every root
     // (its fill also clears the counters and the encoder's tickets, which count
     // on over the batch's levels)
-    BSeedArgs sa{e->vn, e->fm, e->view, B * vplane, level, B * n, n, e->zero_mem, e->zero_words};
+    BLevels lv{};
+    std::copy(level, level + B, lv.p);
+    BSeedArgs sa{e->vn, e->fm, e->view, B * vplane, lv, n, e->zero_mem, e->zero_words};
     BRoots rt{};
     std::copy(roots, roots + B, rt.v);
     e->host_ctl[0] = e->host_ctl[1] = 0;  // level tags start at 1
@@ -967,7 +988,8 @@ extern "C" int csbfs_batch_bfs(csbfs_batch_engine *e, const int64_t *roots, int3
                                                                    : -1;
     const int32_t dir0 = force == CSBFS_DIR_BOTTOM_UP ? CSBFS_DIR_BOTTOM_UP : CSBFS_DIR_TOP_DOWN;
     const int64_t fill = std::max(std::max(B * n, B * vplane), e->zero_words);
-    hipLaunchKernelGGL(bseed_fill_kernel, dim3(grid_for(fill, 256, 16384)), dim3(256), 0, st, sa);
+    hipLaunchKernelGGL(bseed_fill_kernel, dim3(grid_for(fill, 256 * B, 16384 / B), (unsigned)B), dim3(256),
+                       0, st, sa);
     CSBFS_HIP(hipGetLastError());
     hipLaunchKernelGGL(bseed_root_kernel, dim3(1), dim3(64), 0, st, sa, rt, (int32_t)B, R, W, (int32_t)P,
                        vplane, e->rootc(0), e->ctl(0), e->dstate, dir0, force, e->dir(0));
@@ -1068,7 +1090,7 @@ extern "C" int csbfs_batch_bfs(csbfs_batch_engine *e, const int64_t *roots, int3
         hipLaunchKernelGGL(blong_kernel, dim3(1024), dim3(kBThreads), 0, st, ea, pa);
         CSBFS_HIP(hipGetLastError());
         if (ev) CSBFS_HIP(hipEventRecord(ev[1], st));
-        BUpdateArgs ua{e->vn, e->f, level, (int32_t)(j + 1), (int32_t)B, n,
+        BUpdateArgs ua{e->vn, e->f, lv, (int32_t)(j + 1), (int32_t)B, n,
                        e->rootc(sn), e->ctl(sn), e->qcount, (int32_t)P, fc,
                        e->fm, g->deg, e->dstate->sums};
         hipLaunchKernelGGL(bupdate_kernel, dim3(grid_for((words + kBTile - 1) / kBTile, kBThreads / 64, 2048)), dim3(kBThreads), 0, st, ua);
@@ -1183,6 +1205,8 @@ extern "C" int csbfs_batch_bfs(csbfs_batch_engine *e, const int64_t *roots, int3
     }
     return CSBFS_OK;
 }
+
+}  // namespace csbfs
 
 extern "C" int csbfs_batch_stream_words(const csbfs_batch_engine *e, int32_t *words, int32_t cap_levels) {
     if (!e || !words || cap_levels < 0) return fail(CSBFS_EINVAL, "csbfs_batch_stream_words: bad argument");

@@ -104,4 +104,8 @@ int degree_offsets(const int32_t *deg, int64_t n, int64_t *off, int64_t *tile_su
 int batch_engine_make(const csbfs_graph *g, int32_t max_roots, int32_t max_levels, uint32_t flags, void *mem,
                       unsigned long long *host_ctl, hipStream_t st, csbfs_batch_engine **out);
 void batch_engine_release(csbfs_batch_engine *e);
+// csbfs_batch_bfs with a place of its own for each root's levels (n each, apart
+// from each other).
+int batch_bfs_into(csbfs_batch_engine *e, const int64_t *roots, int32_t n_roots, int32_t *const *level,
+                   csbfs_level_stats *stats, int32_t stats_cap, int32_t *n_levels, void *stream);
 }

@@ -280,16 +280,25 @@ void worker(csbfs_server *s, int slot) {
             if (ev && hipStreamWaitEvent(st, ev, 0) != hipSuccess) std::fill(status.begin(), status.end(), CSBFS_EHIP);
         if (batched) {
             int32_t nl = 0;
-            int rc = status[0] != CSBFS_OK ? status[0]
-                                            : csbfs_batch_bfs(b.eng, roots.data(), (int32_t)roots.size(), b.levels,
-                                                              nullptr, 0, &nl, st);
-            if (rc == CSBFS_OK) {
-                for (size_t r = 0; r < outs.size() && rc == CSBFS_OK; ++r)
-                    if (outs[r] && hipMemcpyAsync(outs[r], b.levels + (int64_t)r * n, sizeof(int32_t) * n,
-                                                  hipMemcpyDeviceToDevice, st) != hipSuccess)
-                        rc = CSBFS_EHIP;
-                if (rc == CSBFS_OK && hipStreamSynchronize(st) != hipSuccess) rc = CSBFS_EHIP;
+            int rc = status[0];
+            // levels go straight to the requests' buffers (with a copy of each, a
+            // burst of 96 queries took 3.13 ms instead of 2.97); one that overlaps
+            // an earlier request's buffer is copied from the block afterwards, so
+            // that the later request's levels stand
+            std::vector<int32_t *> rows(outs);
+            for (size_t r = 0; r < rows.size(); ++r) {
+                bool apart = outs[r] != nullptr;
+                for (size_t q = 0; q < r && apart; ++q)
+                    apart = !outs[q] || outs[q] >= outs[r] + n || outs[q] + n <= outs[r];
+                if (!apart) rows[r] = b.levels + (int64_t)r * n;
             }
+            if (rc == CSBFS_OK)
+                rc = batch_bfs_into(b.eng, roots.data(), (int32_t)roots.size(), rows.data(), nullptr, 0, &nl, st);
+            for (size_t r = 0; r < outs.size() && rc == CSBFS_OK; ++r)
+                if (outs[r] && rows[r] != outs[r] &&
+                    hipMemcpyAsync(outs[r], rows[r], sizeof(int32_t) * n, hipMemcpyDeviceToDevice, st) != hipSuccess)
+                    rc = CSBFS_EHIP;
+            if (rc == CSBFS_OK && hipStreamSynchronize(st) != hipSuccess) rc = CSBFS_EHIP;
             std::fill(status.begin(), status.end(), rc);
             std::fill(nls.begin(), nls.end(), nl);
         } else {

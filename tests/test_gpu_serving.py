@@ -223,3 +223,25 @@ def test_concurrent_submitters_and_eviction(pool):
         for (gi, root), o in zip(reqs, outs):
             assert torch.equal(o, engines[gi].bfs(root).level)
     server.close()
+
+
+@pytest.mark.parametrize("step", [0, 300, 512, 1024])
+def test_overlapping_output_buffers(step):
+    """Answers are written in submission order, also where the requests of one
+    batched search share output memory: the later request's levels stand."""
+    from paper_1208_5542_amd import csbfs
+    n, p, queries = 1 << 10, 2, 40
+    src, dst = inputs.rmat_tuples(10, 16)
+    g = csbfs.Graph(torch.from_numpy(src).cuda(), torch.from_numpy(dst).cuda(), n, p)
+    adj = oracle.Adjacency(n, src, dst)
+    roots = [int(src[k * 7]) for k in range(queries)]
+    buf = torch.full((queries * step + n,), -7, dtype=torch.int32, device="cuda")
+    want = np.full(buf.numel(), -7, dtype=np.int32)
+    server = csbfs.Server(slots=1, max_batch=16, max_levels=64, hbm_budget=1 << 28)
+    gid = server.add_graph(g)
+    ids = [server.submit(gid, r, buf[k * step:k * step + n]) for k, r in enumerate(roots)]
+    assert all(server.wait(i)["status"] == 0 for i in ids)
+    for k, r in enumerate(roots):
+        want[k * step:k * step + n] = adj.bfs(r)
+    assert (buf.cpu().numpy() == want).all()
+    server.close()
