@@ -267,9 +267,28 @@ constexpr int kBLongUnroll = 8;   // 64-entry steps per wave in one pass of that
 constexpr float kBatchAlpha = 16.0f, kBatchBeta = 24.0f;
 constexpr int kBPullRounds = 16;  // lane steps before the wave takes over slow lanes
 
+// Direction state of a batched search, carried from level to level.
+struct BDirState {
+    int32_t cur;              // direction of the level expanded next
+    int32_t force;            // < 0: chosen by the rule; else this direction every level
+    unsigned long long prev;  // union frontier size of the level before
+    unsigned long long sums[3];  // union frontier, its adjacency entries, entries still missing a root
+};
+
+// A bottom-up level whose union frontier is below n / kBSparse looks a
+// neighbour up in the frontier's bitmap before it reads its mask: the bitmap
+// stays in L2 where the masks (64 times its size) do not. From kBBitmapVerts
+// vertices on (8 MiB of masks, twice an XCD's L2; at 2^18 vertices the extra
+// step cost 2%). Scale 24, 64 roots whose first level of 9153 vertices goes
+// bottom-up: the batch 36.8 -> 31.7 ms.
+constexpr unsigned long long kBSparse = 16;
+constexpr int64_t kBBitmapVerts = int64_t(1) << 20;
+
 struct BPullArgs {
     uint64_t *vn;              // [n][2]: visit mask, discovery mask
     const uint64_t *fm;        // [n]: frontier masks of the level
+    const uint64_t *ubits;     // [n / 64]: vertices on any root's frontier (null: not known)
+    const BDirState *st;
     const int64_t *pull_off;   // merged rows (global ids) of every vertex
     const uint32_t *pull_col;
     const uint32_t *head;      // [2n]: the first two ids of each merged row
@@ -286,6 +305,25 @@ struct BPullArgs {
     uint32_t *queue_count;
     int32_t *status;
 };
+
+__device__ __forceinline__ bool sparse_level(const BPullArgs &a) {
+    return a.ubits && a.st->prev * kBSparse < (unsigned long long)a.n;
+}
+// Frontier masks of kN neighbours.
+template <int kN>
+__device__ __forceinline__ void gather_masks(const BPullArgs &a, bool sparse, const uint32_t (&c)[kN],
+                                             uint64_t (&m)[kN]) {
+    if (sparse) {
+        uint64_t w[kN];
+#pragma unroll
+        for (int k = 0; k < kN; ++k) w[k] = a.ubits[c[k] >> 6];
+#pragma unroll
+        for (int k = 0; k < kN; ++k) m[k] = (w[k] >> (c[k] & 63)) & 1 ? a.fm[c[k]] : 0ull;
+    } else {
+#pragma unroll
+        for (int k = 0; k < kN; ++k) m[k] = a.fm[c[k]];
+    }
+}
 
 // Bottom-up level. A wave takes 64 vertices (lane = vertex): the two ids of
 // head, then kBPullRounds steps of kBPullUnroll entries per lane. The rows
@@ -307,6 +345,7 @@ __global__ __launch_bounds__(kBThreads) void bpull_kernel(BPullArgs a) {
     // roots whose frontier is not empty: only they can find anything
     const uint64_t active = __ballot(lane < a.B && (!a.rootc || a.rootc[lane] > 0));
     const int64_t wave = tid >> 6, nwaves = nthreads >> 6;
+    const bool sparse = sparse_level(a);
     unsigned long long read = 0;
     for (int64_t v0 = wave * 64; v0 < a.n; v0 += nwaves * 64) {
         const int64_t v = v0 + lane;
@@ -325,8 +364,10 @@ __global__ __launch_bounds__(kBThreads) void bpull_kernel(BPullArgs a) {
         // the row's first two ids come from head, without the row itself
         if (busy) {
             const int32_t nk = re - e < 2 ? (int32_t)(re - e) : 2;
-            const uint64_t m0 = a.fm[hd.x], m1 = a.fm[nk > 1 ? hd.y : hd.x];
-            found |= (m0 | m1) & missing;
+            const uint32_t c[2] = {hd.x, nk > 1 ? hd.y : hd.x};
+            uint64_t m[2];
+            gather_masks<2>(a, sparse, c, m);
+            found |= (m[0] | m[1]) & missing;
             read += (unsigned long long)nk;
             e += nk;
             if (found == missing || e >= re) busy = false;
@@ -341,8 +382,7 @@ __global__ __launch_bounds__(kBThreads) void bpull_kernel(BPullArgs a) {
                 uint64_t m[kBPullWindow];
 #pragma unroll
                 for (int q = 0; q < kBPullWindow; ++q) c[q] = a.pull_col[e + (q < nw ? q : nw - 1)];
-#pragma unroll
-                for (int q = 0; q < kBPullWindow; ++q) m[q] = a.fm[c[q]];
+                gather_masks<kBPullWindow>(a, sparse, c, m);
 #pragma unroll
                 for (int h = 0; h < kBPullWindow / kBPullUnroll; ++h) {
                     const int32_t nk = re - e < kBPullUnroll ? (int32_t)(re - e) : kBPullUnroll;
@@ -409,8 +449,9 @@ __global__ __launch_bounds__(kBThreads) void bpull_kernel(BPullArgs a) {
                 const int64_t pos = se[k] + lane;
                 c[k] = a.pull_col[sl[k] < 0 ? 0 : pos < sr[k] ? pos : sr[k] - 1];
             }
+            gather_masks<kBPullSlots>(a, sparse, c, f);
 #pragma unroll
-            for (int k = 0; k < kBPullSlots; ++k) f[k] = a.fm[c[k]] & smiss[k];  // a repeated last entry adds nothing
+            for (int k = 0; k < kBPullSlots; ++k) f[k] &= smiss[k];  // a repeated last entry adds nothing
 #pragma unroll
             for (int k = 0; k < kBPullSlots; ++k) {
                 if (sl[k] < 0) continue;
@@ -438,6 +479,7 @@ __device__ __forceinline__ void pull_long(const BPullArgs &a) {
     __shared__ uint64_t part[2][kWaves];
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     const int64_t count = (int64_t)*a.queue_count < a.queue_cap ? (int64_t)*a.queue_count : a.queue_cap;
+    const bool sparse = sparse_level(a);
     unsigned long long read = 0;
     int par = 0;
     for (int64_t it = blockIdx.x; it < count; it += gridDim.x) {
@@ -453,9 +495,10 @@ __device__ __forceinline__ void pull_long(const BPullArgs &a) {
                 c[k] = a.pull_col[pos < x.re ? pos : x.re - 1];
             }
             uint64_t any = 0;
+            gather_masks<kBLongUnroll>(a, sparse, c, f);
 #pragma unroll
             for (int k = 0; k < kBLongUnroll; ++k) {
-                f[k] = e0 + 64 * k + lane < x.re ? a.fm[c[k]] & x.miss : 0ull;
+                f[k] = e0 + 64 * k + lane < x.re ? f[k] & x.miss : 0ull;
                 any |= f[k];
             }
             any = __ballot((any & ~got) != 0) ? wave_or64(any) : 0ull;
@@ -494,14 +537,6 @@ __global__ __launch_bounds__(kBThreads) void blong_kernel(BArgs a, BPullArgs pa)
     else if (d == CSBFS_DIR_BOTTOM_UP)
         pull_long(pa);
 }
-
-// Direction state of a batched search, carried from level to level.
-struct BDirState {
-    int32_t cur;              // direction of the level expanded next
-    int32_t force;            // < 0: chosen by the rule; else this direction every level
-    unsigned long long prev;  // union frontier size of the level before
-    unsigned long long sums[3];  // union frontier, its adjacency entries, entries still missing a root
-};
 
 // Beamer's rule over the union of the roots' frontiers (one thread, after the
 // update): top-down turns bottom-up when the frontier's entries times alpha
@@ -571,6 +606,7 @@ struct BUpdateArgs {
     int32_t P;
     const unsigned long long *fcount;  // as in BArgs: 0 visits nothing
     uint64_t *fm;                      // [n]: frontier mask of every vertex (written for all)
+    uint64_t *ubits;                   // [n / 64]: vertices with one
     const int32_t *deg;                // [n]: adjacency entries
     unsigned long long *dsums;         // [3]: union frontier, its entries, entries still missing a root
 };
@@ -611,6 +647,8 @@ __global__ __launch_bounds__(kBThreads) void bupdate_kernel(BUpdateArgs a) {
                     *pv = make_ulonglong2(w.x | nw, 0ull);
                 }
                 a.fm[v] = nw;
+                const uint64_t ub = __ballot(nw != 0);
+                if (lane == 0 && a.n >= kBBitmapVerts) a.ubits[q] = ub;
                 const uint64_t all = a.B == 64 ? ~0ull : ((1ull << a.B) - 1);
                 if (nw || (all & ~(w.x | nw))) {
                     const unsigned long long dg = (unsigned long long)a.deg[v];
@@ -733,6 +771,7 @@ struct csbfs_batch_engine {
     int64_t cap = 0, nseg = 0, nchunk = 0, Smax = 0;
     uint64_t *vn = nullptr, *f = nullptr, *view = nullptr, *arena = nullptr;
     uint64_t *fm = nullptr;           // [n] frontier mask of every vertex (bottom-up levels)
+    uint64_t *ubits = nullptr;        // [n / 64] vertices on any frontier
     BDirState *dstate = nullptr;
     unsigned long long *look = nullptr;  // encoder look-back words [Smax * nseg]
     uint32_t *enc_ticket = nullptr;      // [kTicketStride * Smax], after look
@@ -785,11 +824,11 @@ namespace {
 // Device bytes of every buffer of a batch engine; total() is the size of
 // the one block they are carved from (each buffer 256-byte aligned).
 struct BatchSizes {
-    int64_t vis, f, view, arena, chunk, queue, qoff, zero, fm, dstate, pqueue;
+    int64_t vis, f, view, arena, chunk, queue, qoff, zero, fm, ubits, dstate, pqueue;
     int64_t hdr, stride;  // words before the first record, words per record
     int64_t total() const {
         int64_t t = 0;
-        for (int64_t b : {vis, f, view, arena, chunk, queue, qoff, zero, fm, dstate, pqueue})
+        for (int64_t b : {vis, f, view, arena, chunk, queue, qoff, zero, fm, ubits, dstate, pqueue})
             t += align_up(b > 0 ? b : 1);
         return t;
     }
@@ -817,6 +856,7 @@ BatchSizes batch_sizes(const csbfs_graph *g, int64_t B, int64_t L, uint32_t flag
     z.stride = 3 + B + B * P + 2 * Smax;
     z.zero = 8 * (z.hdr + slots * z.stride) + 8 * Smax * enc_segments(g->R) + 4 * kTicketStride * Smax;
     z.fm = 8 * n;
+    z.ubits = 8 * (n / 64);
     z.dstate = (int64_t)sizeof(BDirState);
     return z;
 }
@@ -905,6 +945,7 @@ int batch_engine_make(const csbfs_graph *g, int32_t max_roots, int32_t max_level
     e->look = e->recs + ((int64_t)max_levels + 1) * z.stride;
     e->enc_ticket = reinterpret_cast<uint32_t *>(e->look + e->Smax * e->nseg);
     e->fm = (uint64_t *)carve(z.fm);
+    e->ubits = (uint64_t *)carve(z.ubits);
     e->dstate = (BDirState *)carve(z.dstate);
     e->pqueue = (BPullItem *)carve(z.pqueue);
     e->pqueue_cap = pull_long_rows(g->nnz);
@@ -1084,6 +1125,8 @@ int batch_bfs_into(csbfs_batch_engine *e, const int64_t *roots, int32_t n_roots,
         pa.rootc = j < e->L ? e->rootc(sj) : nullptr;
         pa.edges = e->edges(sj);
         pa.fcount = fc;
+        pa.st = e->dstate;
+        pa.ubits = j > 0 && n >= kBBitmapVerts ? e->ubits : nullptr;  // no update made f^0
         hipLaunchKernelGGL(bpull_kernel, dim3(grid), dim3(kBThreads), 0, st, pa);
         CSBFS_HIP(hipGetLastError());
         // long rows: 1024 workgroups beat 512, 2048 and 4096 (a sweep, within 2%)
@@ -1092,7 +1135,7 @@ int batch_bfs_into(csbfs_batch_engine *e, const int64_t *roots, int32_t n_roots,
         if (ev) CSBFS_HIP(hipEventRecord(ev[1], st));
         BUpdateArgs ua{e->vn, e->f, lv, (int32_t)(j + 1), (int32_t)B, n,
                        e->rootc(sn), e->ctl(sn), e->qcount, (int32_t)P, fc,
-                       e->fm, g->deg, e->dstate->sums};
+                       e->fm, e->ubits, g->deg, e->dstate->sums};
         hipLaunchKernelGGL(bupdate_kernel, dim3(grid_for((words + kBTile - 1) / kBTile, kBThreads / 64, 2048)), dim3(kBThreads), 0, st, ua);
         CSBFS_HIP(hipGetLastError());
         if (ev) CSBFS_HIP(hipEventRecord(ev[2], st));

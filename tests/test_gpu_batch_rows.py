@@ -71,3 +71,40 @@ def test_bottom_up_rows(left, p):
             vis |= ((ref[b] >= 0) & (ref[b] <= k)).astype(np.int64) << b
         want = sum(_read(rows[v], fm, active & ~int(vis[v])) for v in range(n) if rows[v] and active & ~int(vis[v]))
         assert r.stats[k]["direction"] == 1 and r.stats[k]["edges"] == want, k
+
+
+@pytest.mark.parametrize("n", [(1 << 20) - 64, 1 << 20, (1 << 20) + 64])
+@pytest.mark.parametrize("dense", [False, True])
+def test_bottom_up_through_the_frontier_bitmap(n, dense):
+    """Sparse and wide union frontiers on either side of the sizes that look
+    neighbours up in the frontier's bitmap: same levels, same entries read."""
+    from paper_1208_5542_amd import csbfs
+    rng = np.random.default_rng(n + dense)
+    used = rng.choice(n, 120000 if dense else 3000, replace=False)
+    hub = int(used[0])
+    src = np.concatenate([used[rng.integers(0, used.size, 40000)], np.full(6000, hub), used if dense else used[:2]])
+    dst = np.concatenate([used[rng.integers(0, used.size, 40000)], used[rng.integers(0, used.size, 6000)],
+                          np.full(used.size if dense else 2, int(used[1]))])
+    roots = [int(used[1]), hub, int(used[7]), int(dst[5])]
+    g = csbfs.Graph(torch.from_numpy(src).cuda(), torch.from_numpy(dst).cuda(), n, 1)
+    r = csbfs.BatchEngine(g, max_roots=4, max_levels=64, flags=csbfs.FLAG_BOTTOM_UP_ONLY).bfs(roots)
+    torch.cuda.synchronize()
+    adj = oracle.Adjacency(n, src, dst)
+    ref = np.stack([adj.bfs(s) for s in roots])
+    assert (r.level.cpu().numpy() == ref).all()
+    rows = {}
+    for a, b in zip(src.tolist(), dst.tolist()):
+        rows.setdefault(a, []).append(b)
+        rows.setdefault(b, []).append(a)
+    rows = {v: sorted(x, reverse=True) for v, x in rows.items()}
+    for k in range(r.n_levels):
+        fm, vis, active = {}, {}, 0
+        for b in range(len(roots)):
+            for v in np.flatnonzero(ref[b] == k).tolist():
+                fm[v] = fm.get(v, 0) | 1 << b
+                active |= 1 << b
+            for v in np.flatnonzero((ref[b] >= 0) & (ref[b] <= k)).tolist():
+                vis[v] = vis.get(v, 0) | 1 << b
+        fm = {v: fm.get(v, 0) for v in rows}
+        want = sum(_read(x, fm, active & ~vis.get(v, 0)) for v, x in rows.items() if active & ~vis.get(v, 0))
+        assert r.stats[k]["edges"] == want, k
