@@ -34,7 +34,10 @@
  *     allocates device memory nor synchronizes anything but its own stream.
  *     The convenience calls csbfs_graph_build and csbfs_engine_create
  *     allocate those same buffers themselves (hipMalloc) and free them in
- *     csbfs_graph_free and csbfs_engine_free. The codec calls allocate nothing.
+ *     csbfs_graph_free and csbfs_engine_free. Buffers of graphs and of their
+ *     builds that are freed are kept for later builds, up to 2 GiB per process,
+ *     and go back to the device when an allocation of the library needs them.
+ *     The codec calls allocate nothing.
  *
  * The WAH-64 stream format (Sec. IV, Table 3 and the 32-bit example in the
  * source of that table). A stream encodes N bits b[0..N) as 63-bit groups;
@@ -124,7 +127,7 @@ int csbfs_graph_build_into(const int64_t *src, const int64_t *dst, int64_t n_tup
                            void *stream, csbfs_graph **out);
 
 /* Release a graph handle. A graph built by csbfs_graph_build also frees its
- * device memory (hipFree, which waits for work still using it); one built by
+ * device memory (after the work on its device that may still use it); one built by
  * csbfs_graph_build_into leaves the caller's buffer alone and makes no HIP
  * call. NULL is accepted. */
 int csbfs_graph_free(csbfs_graph *g);
