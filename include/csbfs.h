@@ -615,7 +615,7 @@ int csbfs_wah_encode(const uint64_t *bits, const uint64_t *mask, int64_t nbits, 
  * inside the library (one per GPU, held until the process ends), which
  * bounds nbits by csbfs_wah_noalloc_max_bits() (above 4 * 10^9 bits): a
  * larger nbits fails with EINVAL. The array is cleared by a kernel at every
- * call (no memset node). Every call on one GPU shares that array: calls
+ * call that uses it (above 129024 bits; no memset node). Every call on one GPU shares that array: calls
  * that overlap in time on one GPU (concurrent streams or threads) race and
  * must be serialized by the caller. Asynchronous.
  */
