@@ -162,6 +162,19 @@ def _ptr(t: torch.Tensor | None):
     return ctypes.c_void_p(t.data_ptr())
 
 
+# A call on a stream of the caller's that uses tensors made, and read back, on
+# the current one: it starts after what is queued there, and what is queued
+# there next (a read of the result, a reuse of freed scratch) comes after it.
+def _enter(stream):
+    if stream is not None:
+        stream.wait_stream(torch.cuda.current_stream())
+
+
+def _leave(stream):
+    if stream is not None:
+        torch.cuda.current_stream().wait_stream(stream)
+
+
 def version() -> int:
     return lib().csbfs_version()
 
@@ -541,7 +554,9 @@ def wah_decode_or(words: torch.Tensor, nbits: int, dst: torch.Tensor | None = No
         dst = torch.zeros(max((nbits + 63) // 64, 1), dtype=torch.int64, device="cuda")
     status = torch.zeros(1, dtype=torch.int32, device="cuda")
     ws = workspace if workspace is not None else wah_workspace(nbits)
-    _check(lib().csbfs_wah_decode_or(_ptr(words) if words.numel() else None, words.numel(), nbits,
-                                     _ptr(dst), _ptr(status), _ptr(ws), ws.numel(), _stream(stream)),
-           "csbfs_wah_decode_or")
+    _enter(stream)
+    rc = lib().csbfs_wah_decode_or(_ptr(words) if words.numel() else None, words.numel(), nbits,
+                                   _ptr(dst), _ptr(status), _ptr(ws), ws.numel(), _stream(stream))
+    _leave(stream)
+    _check(rc, "csbfs_wah_decode_or")
     return dst, int(status.item())
