@@ -542,8 +542,11 @@ def wah_encode(bits: torch.Tensor, nbits: int, mask: torch.Tensor | None = None,
     out = torch.empty(cap, dtype=torch.int64, device="cuda")
     nw = torch.zeros(1, dtype=torch.int64, device="cuda")
     ws = workspace if workspace is not None else wah_workspace(nbits)
-    _check(lib().csbfs_wah_encode(_ptr(bits), _ptr(mask), nbits, _ptr(out), cap, _ptr(nw),
-                                  _ptr(ws), ws.numel(), _stream(stream)), "csbfs_wah_encode")
+    _enter(stream)
+    rc = lib().csbfs_wah_encode(_ptr(bits), _ptr(mask), nbits, _ptr(out), cap, _ptr(nw),
+                                _ptr(ws), ws.numel(), _stream(stream))
+    _leave(stream)
+    _check(rc, "csbfs_wah_encode")
     return out[: int(nw.item())]
 
 

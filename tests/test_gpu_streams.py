@@ -41,3 +41,12 @@ def test_decode_status_and_result_on_another_stream():
     assert status == 0 and (from_words(dst, NBITS) == bits).all()
     _, status = csbfs.wah_decode_or(bad, NBITS, stream=_busy_stream())
     assert status != 0
+
+
+def test_encode_length_on_another_stream():
+    from paper_1208_5542_amd import csbfs
+    bits = _bits()
+    dev = to_words(bits)
+    torch.cuda.synchronize()
+    words = csbfs.wah_encode(dev, NBITS, stream=_busy_stream())
+    assert u64(words).tolist() == oracle.wah_encode(bits).tolist()
