@@ -161,7 +161,7 @@ __global__ __launch_bounds__(kBThreads) void bexpand_kernel(BArgs a) {
                     rs = rp[0];
                     deg = rp[1] - rs;
                 }
-                const int32_t items = deg > kBigRow ? (deg + kBigChunk - 1) / kBigChunk : 0;
+                const int32_t items = row_items(deg);
                 const int32_t items_incl = wave_incl_scan_i32(items);
                 const int32_t items_total = __shfl(items_incl, 63, 64);
                 if (items_total) {
@@ -180,7 +180,7 @@ __global__ __launch_bounds__(kBThreads) void bexpand_kernel(BArgs a) {
                                 it.block = (int32_t)blk;
                                 it.u_local = (int32_t)ul;
                                 it.start = rs + c * kBigChunk;
-                                it.end = min(rs + deg, rs + (c + 1) * kBigChunk);
+                                it.end = it.start + min(deg - c * kBigChunk, kBigChunk);
                                 a.queue[a.qoff[i] + qpos + c] = it;
                             }
                         }
@@ -235,21 +235,22 @@ __device__ __forceinline__ void push_long(const BArgs &a) {
         before += count;
         for (int64_t kk = first; kk < count; kk += nwaves) {
             const BItem it = queue[kk];
-            const uint32_t *colb = a.col + a.col_base[it.block];
-            for (int32_t e0 = it.start; e0 < it.end; e0 += 64 * kBUnroll) {
+            const uint32_t *colb = a.col + a.col_base[it.block] + it.start;
+            const int32_t len = it.end - it.start;  // places from the item's first: its end may lie near 2^31
+            for (int32_t e0 = 0; e0 < len; e0 += 64 * kBUnroll) {
                 int64_t v[kBUnroll];
                 uint64_t m[kBUnroll];
                 bool ok[kBUnroll];
 #pragma unroll
                 for (int k = 0; k < kBUnroll; ++k) {
                     const int32_t e = e0 + 64 * k + lane;
-                    ok[k] = e < it.end;
-                    v[k] = vbase + colb[ok[k] ? e : it.end - 1];  // clamped to the item's last entry
+                    ok[k] = e < len;
+                    v[k] = vbase + colb[ok[k] ? e : len - 1];  // clamped to the item's last entry
                     m[k] = it.mask;
                 }
                 brelax(a, v, m, ok);
             }
-            edges += (unsigned long long)(it.end - it.start);
+            edges += (unsigned long long)len;
         }
     }
     block_add<kBThreads / 64>(edges, a.edges);

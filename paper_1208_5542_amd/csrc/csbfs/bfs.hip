@@ -279,7 +279,7 @@ __device__ __forceinline__ void expand_tile(const ExpandArgs &a, int32_t r, int6
             gstart = a.col_base[b] + rs;
             u = (int32_t)(j * a.R + ul);
         }
-        const int32_t items = deg > kBigRow ? (deg + kBigChunk - 1) / kBigChunk : 0;
+        const int32_t items = row_items(deg);
         const int32_t items_incl = wave_incl_scan_i32(items);
         const int32_t items_total = __shfl(items_incl, 63, 64);
         if (items_total) {

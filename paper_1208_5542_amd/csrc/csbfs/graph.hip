@@ -181,7 +181,8 @@ __global__ __launch_bounds__(kThreads) void k_degree(const int32_t *row_ptr, int
             const int32_t *rp = row_ptr + ((int64_t)i * P + j) * (R + 1) + ul;
             const int32_t len = rp[1] - rp[0];
             d += len;
-            if (len > kBigRow) atomicAdd(&big[i], (unsigned long long)((len + kBigChunk - 1) / kBigChunk));
+            const int32_t items = row_items(len);
+            if (items) atomicAdd(&big[i], (unsigned long long)items);
         }
         if (ok) deg[u] = d;
     }
@@ -316,13 +317,17 @@ __global__ __launch_bounds__(kThreads) void k_pull_long(const int32_t *row_ptr, 
         const int32_t rs = rp[0], len = rp[1] - rs;
         const uint32_t *src = col + col_base[b] + rs;
         const uint32_t base = (uint32_t)(j * R);
-        for (int32_t e0 = threadIdx.x; e0 < len; e0 += kUn * kThreads) {
+        // 64-bit places: a row may end within one step of 2^31
+        for (int64_t e0 = threadIdx.x; e0 < len; e0 += kUn * kThreads) {
             uint32_t id[kUn];
 #pragma unroll
-            for (int u = 0; u < kUn; ++u) id[u] = src[min(e0 + u * kThreads, len - 1)];
+            for (int u = 0; u < kUn; ++u) {
+                const int64_t e = e0 + u * kThreads;
+                id[u] = src[e < len ? e : len - 1];
+            }
 #pragma unroll
             for (int u = 0; u < kUn; ++u) {
-                const int32_t e = e0 + u * kThreads;
+                const int64_t e = e0 + u * kThreads;
                 if (e < len) put_id(base + id[u], d + e, first, v, pull_col, head);
             }
         }

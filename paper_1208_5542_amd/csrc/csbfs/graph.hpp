@@ -13,6 +13,8 @@ namespace csbfs {
 // word's wavefront.
 constexpr int kBigRow = 128;
 constexpr int kBigChunk = 512;
+// Queue items of a row of len entries; rows may have up to 2^31 - 2.
+__host__ __device__ inline int32_t row_items(int32_t len) { return len > kBigRow ? (len - 1) / kBigChunk + 1 : 0; }
 
 // Alignment of every array carved out of a caller's buffer.
 constexpr int64_t kAlign = 256;
