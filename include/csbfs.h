@@ -100,7 +100,9 @@ typedef struct csbfs_graph csbfs_graph;
  * Block (i, j) holds, for every source u in R_j, its neighbours in R_i as a
  * CSR row (int32 row offsets, uint32 local column ids). The directory vector
  * V_{i,j} (Eq. dir-vec) is the non-empty-row bitmap of block (i, j). The
- * input buffers are only read and may be freed after the call. Blocking.
+ * input buffers are only read and may be freed after the call. The build's
+ * scratch is allocated too; if the larger one that sorting takes cannot be had,
+ * the smaller one of csbfs_graph_build_into is tried. Blocking.
  * Errors: EINVAL (null pointers, n_tuples < 0), ERANGE (n or p not
  * admissible, a tuple id outside [0, n)), EOVERFLOW, ECORRUPT (the built
  * CSR failed its consistency check: a column id outside its block or an
@@ -119,8 +121,13 @@ int csbfs_graph_build(const int64_t *src, const int64_t *dst, int64_t n_tuples, 
  * both buffers must start at a multiple of 256 bytes. The handle itself is
  * small host memory; csbfs_graph_free releases it and never frees the
  * caller's buffer. No device allocation; synchronizes `stream` only
- * (blocking). Errors: as csbfs_graph_build, plus EINVAL (null or misaligned
- * buffer) and ENOSPACE (a buffer smaller than the query gives).
+ * (blocking). Builds of 2^18 to 2^31 adjacency entries (2 n_tuples) sort them,
+ * which takes about 8.25 bytes of scratch an entry; where scratch_bytes does
+ * not cover that but is at least 4 p n + p n / 64 + 5 n_tuples / 8 + 16 p^2 +
+ * 8192, the same graph is built by counting instead, several times slower on
+ * large graphs. Errors: as csbfs_graph_build, plus EINVAL (null or misaligned
+ * buffer) and ENOSPACE (graph_mem smaller than the query gives, or a scratch
+ * too small for both).
  */
 int csbfs_graph_build_into(const int64_t *src, const int64_t *dst, int64_t n_tuples, int64_t n, int32_t p,
                            void *graph_mem, size_t graph_bytes, void *scratch, size_t scratch_bytes,
@@ -251,7 +258,7 @@ typedef struct csbfs_search_config {
 /* Byte sizes of the caller-owned device buffers. */
 typedef struct csbfs_sizes {
     int64_t graph_bytes;          /* a built graph (csbfs_graph_build_into graph_mem) */
-    int64_t build_scratch_bytes;  /* temporaries of csbfs_graph_build_into */
+    int64_t build_scratch_bytes;  /* temporaries of csbfs_graph_build_into (see there for less) */
     int64_t workspace_bytes;      /* one search (csbfs_bfs_ws workspace) */
     int64_t alignment;            /* every buffer starts at a multiple of this (256) */
 } csbfs_sizes;

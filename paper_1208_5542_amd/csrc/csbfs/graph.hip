@@ -8,6 +8,7 @@
 // entries (radix.hip) or, for few or very many of them, by a counting pass and
 // a scatter whose rows are sorted afterwards (sort.hip); row offsets come from
 // a per-block scan (tile sums, scan of tile sums, local scans).
+#include <algorithm>
 #include <vector>
 
 #include "device.hpp"
@@ -20,31 +21,35 @@ constexpr int kThreads = 256;
 constexpr int kTileItems = 4;
 constexpr int kTile = kThreads * kTileItems;
 
-__device__ __forceinline__ int wave_incl_scan_ll(long long &v) {
-    const int lane = threadIdx.x & 63;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        long long t = __shfl_up(v, d, 64);
-        if (lane >= d) v += t;
-    }
-    return 0;
+// Scans of rows: of their counts (sums), or (kEnds) of the places after their
+// last entries, 0 for an empty row (maxima, as places grow with the rows).
+template <bool kEnds>
+__device__ __forceinline__ long long scan_op(long long a, long long b) {
+    return kEnds ? (a > b ? a : b) : a + b;
 }
 
+// Exclusive over the workgroup, from 0; the total in *total.
+template <bool kEnds>
 __device__ long long block_excl_scan_ll(long long v, long long *total) {
     __shared__ long long ws[kThreads / 64];
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     long long incl = v;
-    wave_incl_scan_ll(incl);
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const long long t = __shfl_up(incl, d, 64);
+        if (lane >= d) incl = scan_op<kEnds>(incl, t);
+    }
     if (lane == 63) ws[wid] = incl;
+    const long long up = __shfl_up(incl, 1, 64);
     __syncthreads();
     long long before = 0, tot = 0;
     for (int k = 0; k < kThreads / 64; ++k) {
-        if (k < wid) before += ws[k];
-        tot += ws[k];
+        if (k < wid) before = scan_op<kEnds>(before, ws[k]);
+        tot = scan_op<kEnds>(tot, ws[k]);
     }
     __syncthreads();
     *total = tot;
-    return before + incl - v;
+    return lane > 0 ? scan_op<kEnds>(before, up) : before;
 }
 
 __global__ void k_count(const int64_t *src, const int64_t *dst, int64_t m, int64_t n, int64_t R,
@@ -62,33 +67,29 @@ __global__ void k_count(const int64_t *src, const int64_t *dst, int64_t m, int64
     }
 }
 
-// A row's entries: cnt[row], less row_start[row] where that is given (cnt is
-// then the place after its last entry; places are below 2^32).
-__device__ __forceinline__ int32_t row_count(const int32_t *cnt, const int32_t *row_start, int64_t row) {
-    return (int32_t)((uint32_t)cnt[row] - (row_start ? (uint32_t)row_start[row] : 0u));
-}
-
-// tile sums of every block's row counts: sums[b * ntile + t]
-__global__ __launch_bounds__(kThreads) void k_tile_sum(const int32_t *cnt, const int32_t *row_start, int64_t R,
+// tile totals of every block's rows, cnt[b * stride + u]: sums[b * ntile + t]
+template <bool kEnds>
+__global__ __launch_bounds__(kThreads) void k_tile_sum(const int32_t *cnt, int64_t stride, int64_t R,
                                                        int64_t ntile, long long *sums) {
     const int64_t t = blockIdx.x, b = blockIdx.y;
     long long s = 0;
     for (int64_t k = threadIdx.x; k < kTile; k += kThreads) {
         const int64_t u = t * kTile + k;
-        if (u < R) s += row_count(cnt, row_start, b * R + u);
+        if (u < R) s = scan_op<kEnds>(s, (uint32_t)cnt[b * stride + u]);
     }
     __shared__ long long red[kThreads / 64];
-    for (int d = 32; d > 0; d >>= 1) s += __shfl_xor(s, d, 64);
+    for (int d = 32; d > 0; d >>= 1) s = scan_op<kEnds>(s, __shfl_xor(s, d, 64));
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
     __syncthreads();
     if (threadIdx.x == 0) {
         long long tot = 0;
-        for (int k = 0; k < kThreads / 64; ++k) tot += red[k];
+        for (int k = 0; k < kThreads / 64; ++k) tot = scan_op<kEnds>(tot, red[k]);
         sums[b * ntile + t] = tot;
     }
 }
 
-// in-place exclusive scan of each block's tile sums; block totals to nnz[b]
+// in-place exclusive scan of each block's tile totals; block totals to nnz[b]
+template <bool kEnds>
 __global__ __launch_bounds__(kThreads) void k_tile_scan(long long *sums, int64_t ntile,
                                                         long long *nnz) {
     const int64_t b = blockIdx.x;
@@ -97,35 +98,40 @@ __global__ __launch_bounds__(kThreads) void k_tile_scan(long long *sums, int64_t
         const int64_t t = base + threadIdx.x;
         const long long v = t < ntile ? sums[b * ntile + t] : 0;
         long long tot;
-        const long long ex = block_excl_scan_ll(v, &tot);
-        if (t < ntile) sums[b * ntile + t] = carry + ex;
-        carry += tot;
+        const long long ex = block_excl_scan_ll<kEnds>(v, &tot);
+        if (t < ntile) sums[b * ntile + t] = scan_op<kEnds>(carry, ex);
+        carry = scan_op<kEnds>(carry, tot);
     }
     if (threadIdx.x == 0) nnz[b] = carry;
 }
 
-// row_ptr[b * (R + 1) + u] = exclusive prefix of row counts within block b;
-// the counts become the scatter cursors (cursor[u] = row_ptr[u]).
-__global__ __launch_bounds__(kThreads) void k_tile_apply(int32_t *cnt, const int32_t *row_start, int64_t R, int64_t ntile,
-                                                         const long long *sums, int32_t *row_ptr) {
+// row_ptr[b * (R + 1) + u] = entries of block b's rows before u. Counts become
+// the scatter cursors (cursor[u] = row_ptr[u]); ends lie in row_ptr itself
+// (stride R + 1), and each thread replaces those it read. An end is a place
+// among all blocks' entries, so the block's first place is taken off.
+template <bool kEnds>
+__global__ __launch_bounds__(kThreads) void k_tile_apply(int32_t *cnt, int64_t stride, int64_t R, int64_t ntile,
+                                                         const long long *sums, const int64_t *col_base, int32_t *row_ptr) {
     const int64_t t = blockIdx.x, b = blockIdx.y;
     const int64_t u0 = t * kTile + threadIdx.x * kTileItems;
+    const long long first = kEnds ? col_base[b] : 0;
     long long v[kTileItems];
     long long mine = 0;
     for (int k = 0; k < kTileItems; ++k) {
         const int64_t u = u0 + k;
-        v[k] = u < R ? row_count(cnt, row_start, b * R + u) : 0;
-        mine += v[k];
+        v[k] = u < R ? (uint32_t)cnt[b * stride + u] : 0;
+        mine = scan_op<kEnds>(mine, v[k]);
     }
     long long tot;
-    long long x = sums[b * ntile + t] + block_excl_scan_ll(mine, &tot);
+    const long long before = block_excl_scan_ll<kEnds>(mine, &tot);
+    long long x = scan_op<kEnds>(scan_op<kEnds>(sums[b * ntile + t], before), first);
     for (int k = 0; k < kTileItems; ++k) {
         const int64_t u = u0 + k;
         if (u < R) {
-            row_ptr[b * (R + 1) + u] = (int32_t)x;
-            cnt[b * R + u] = (int32_t)x;
-            x += v[k];
-            if (u == R - 1) row_ptr[b * (R + 1) + R] = (int32_t)x;
+            row_ptr[b * (R + 1) + u] = (int32_t)(x - first);
+            if (!kEnds) cnt[b * stride + u] = (int32_t)x;
+            x = scan_op<kEnds>(x, v[k]);
+            if (u == R - 1) row_ptr[b * (R + 1) + R] = (int32_t)(x - first);
         }
     }
 }
@@ -345,6 +351,9 @@ __global__ void k_live(const int32_t *deg, int64_t n, uint64_t *live) {
 // scattering and sorting rows. R-MAT, 4 x 4, in us (sort, else): 2^17 entries
 // 313, 321; 2^18 324, 412; 2^20 342, 533; 2^25 1820, 5850; 2^31 (8 x 8) 145 ms,
 // 397. Above, the places do not fit 32 bits.
+// The sort needs 8.25 bytes of scratch an entry, where counting needs 4 p n and
+// a quarter byte an entry: at 2^31 entries on the 8 x 8 grid 16.5 GiB against
+// 2.5. A build that cannot have the sort's scratch counts instead.
 constexpr int64_t kSortMin = int64_t(1) << 18, kSortMax = int64_t(1) << 31;
 
 constexpr int kMiscWords = 64;  // build flags and counters: err, sort queue counts, check, big items
@@ -360,7 +369,7 @@ int check_sizes(int64_t n, int64_t n_tuples, int32_t p, const char *who) {
 
 }  // namespace
 
-int graph_layout(int64_t n, int64_t n_tuples, int32_t p, GraphLayout *L) {
+int graph_layout(int64_t n, int64_t n_tuples, int32_t p, GraphLayout *L, bool sort) {
     const int rc = check_sizes(n, n_tuples, p, "graph layout");
     if (rc) return rc;
     GraphLayout g{};
@@ -390,10 +399,11 @@ int graph_layout(int64_t n, int64_t n_tuples, int32_t p, GraphLayout *L) {
     g.small = take(8 * 64);
     g.graph_bytes = o;
     o = 0;
-    g.sorted = g.nnz >= kSortMin && g.nnz <= kSortMax;
-    g.radix = g.sorted ? take(radix_scratch_bytes(g.nnz)) : 0;
-    g.row_start = g.sorted ? take(4 * g.B * g.R) : 0;
-    g.cnt = take(4 * g.B * g.R);
+    g.sorted = sort && g.nnz >= kSortMin && g.nnz <= kSortMax;
+    if (g.sorted)
+        g.radix = take(radix_scratch_bytes(g.nnz));  // the rows' ends lie in row_ptr
+    else
+        g.cnt = take(4 * g.B * g.R);
     g.sums = take(8 * g.B * g.ntile);
     g.nnzb = take(8 * g.B);
     g.misc = take(8 * (kMiscWords + g.P));
@@ -428,6 +438,10 @@ extern "C" int csbfs_graph_build_into(const int64_t *src, const int64_t *dst, in
     if (!graph_mem || !scratch) return fail(CSBFS_EINVAL, "csbfs_graph_build_into: null graph or scratch buffer");
     if ((uintptr_t)graph_mem % kAlign || (uintptr_t)scratch % kAlign)
         return fail(CSBFS_EINVAL, "csbfs_graph_build_into: buffers must be 256-byte aligned");
+    if (L.sorted && (int64_t)scratch_bytes < L.scratch_bytes) {
+        rc = graph_layout(n, n_tuples, p, &L, false);
+        if (rc) return rc;
+    }
     if ((int64_t)graph_bytes < L.graph_bytes || (int64_t)scratch_bytes < L.scratch_bytes)
         return fail(CSBFS_ENOSPACE, "csbfs_graph_build_into: graph or scratch buffer smaller than "
                                     "csbfs_layout_query gives");
@@ -453,20 +467,19 @@ extern "C" int csbfs_graph_build_into(const int64_t *src, const int64_t *dst, in
     g->live = (uint64_t *)(gm + L.live);
     g->qoff = (int64_t *)(gm + L.qoff);
     g->scratch = (unsigned long long *)(gm + L.small);
-    int32_t *cnt = (int32_t *)(sm + L.cnt);
+    // the rows' counts, or (sorted) their ends, `stride` of them per block
+    int32_t *cnt = L.sorted ? g->row_ptr : (int32_t *)(sm + L.cnt);
+    const int64_t stride = L.sorted ? R + 1 : R;
     long long *sums = (long long *)(sm + L.sums);
     long long *nnzb = (long long *)(sm + L.nnzb);
     unsigned long long *misc = (unsigned long long *)(sm + L.misc);
     int32_t *err = (int32_t *)misc;
     unsigned long long *qcount = misc + 8, *chk = misc + 16, *big = misc + kMiscWords;
 
-    CSBFS_HIP(hipMemsetAsync(cnt, 0, sizeof(int32_t) * B * R, st));
+    CSBFS_HIP(hipMemsetAsync(cnt, 0, sizeof(int32_t) * B * stride, st));
     CSBFS_HIP(hipMemsetAsync(misc, 0, sizeof(unsigned long long) * (kMiscWords + p), st));
-    int32_t *row_start = nullptr;
     if (L.sorted) {
-        row_start = (int32_t *)(sm + L.row_start);
-        CSBFS_HIP(hipMemsetAsync(row_start, 0, sizeof(int32_t) * B * R, st));
-        rc = sort_entries(src, dst, n_tuples, n, p, sm + L.radix, g->col, g->col, row_start, cnt, err, st);
+        rc = sort_entries(src, dst, n_tuples, n, p, sm + L.radix, g->col, g->col, cnt, err, st);
         if (rc) return rc;
     } else if (n_tuples > 0) {
         hipLaunchKernelGGL(k_count, dim3(grid_for(n_tuples, kThreads, 65536)), dim3(kThreads), 0, st, src,
@@ -475,10 +488,10 @@ extern "C" int csbfs_graph_build_into(const int64_t *src, const int64_t *dst, in
     }
     int32_t herr = 0;
     CSBFS_HIP(hipMemcpyAsync(&herr, err, sizeof(herr), hipMemcpyDeviceToHost, st));
-    hipLaunchKernelGGL(k_tile_sum, dim3((unsigned)ntile, (unsigned)B), dim3(kThreads), 0, st,
-                       (const int32_t *)cnt, (const int32_t *)row_start, R, ntile, sums);
+    hipLaunchKernelGGL(L.sorted ? k_tile_sum<true> : k_tile_sum<false>, dim3((unsigned)ntile, (unsigned)B), dim3(kThreads), 0, st,
+                       (const int32_t *)cnt, stride, R, ntile, sums);
     CSBFS_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_tile_scan, dim3((unsigned)B), dim3(kThreads), 0, st, sums, ntile, nnzb);
+    hipLaunchKernelGGL(L.sorted ? k_tile_scan<true> : k_tile_scan<false>, dim3((unsigned)B), dim3(kThreads), 0, st, sums, ntile, nnzb);
     CSBFS_HIP(hipGetLastError());
     std::vector<long long> nnz(B);
     CSBFS_HIP(hipMemcpyAsync(nnz.data(), nnzb, sizeof(long long) * B, hipMemcpyDeviceToHost, st));
@@ -487,6 +500,7 @@ extern "C" int csbfs_graph_build_into(const int64_t *src, const int64_t *dst, in
     std::vector<int64_t> base(B + 1, 0);
     int64_t maxb = 0;
     for (int64_t b = 0; b < B; ++b) {
+        if (L.sorted) nnz[b] = std::max<long long>(nnz[b] - base[b], 0);  // from the block's last end
         if (nnz[b] >= ((long long)1 << 31) - 1)
             return fail(CSBFS_EOVERFLOW, "csbfs_graph_build_into: a sub-block has >= 2^31 entries");
         base[b + 1] = base[b] + nnz[b];
@@ -495,8 +509,9 @@ extern "C" int csbfs_graph_build_into(const int64_t *src, const int64_t *dst, in
     const int64_t total = base[B];
     if (total != L.nnz) return fail(CSBFS_ECORRUPT, "csbfs_graph_build_into: adjacency count mismatch");
     CSBFS_HIP(hipMemcpyAsync(g->col_base, base.data(), sizeof(int64_t) * (B + 1), hipMemcpyHostToDevice, st));
-    hipLaunchKernelGGL(k_tile_apply, dim3((unsigned)ntile, (unsigned)B), dim3(kThreads), 0, st, cnt,
-                       (const int32_t *)row_start, R, ntile, (const long long *)sums, g->row_ptr);
+    hipLaunchKernelGGL(L.sorted ? k_tile_apply<true> : k_tile_apply<false>, dim3((unsigned)ntile, (unsigned)B),
+                       dim3(kThreads), 0, st, cnt, stride, R, ntile, (const long long *)sums,
+                       (const int64_t *)g->col_base, g->row_ptr);
     CSBFS_HIP(hipGetLastError());
     if (n_tuples > 0 && !L.sorted) {
         hipLaunchKernelGGL(k_scatter, dim3(grid_for(n_tuples, kThreads, 65536)), dim3(kThreads), 0, st,
@@ -576,6 +591,8 @@ extern "C" int csbfs_graph_build(const int64_t *src, const int64_t *dst, int64_t
     rc = device_take((size_t)L.graph_bytes, &gm);
     if (rc) return rc;
     rc = device_take((size_t)L.scratch_bytes, &sm);
+    if (rc && L.sorted && graph_layout(n, n_tuples, p, &L, false) == CSBFS_OK)
+        rc = device_take((size_t)L.scratch_bytes, &sm);  // no room to sort: count
     if (rc) {
         device_give(gm);
         return rc;

@@ -28,16 +28,17 @@ inline int64_t big_items_bound(int64_t nnz) { return nnz / kBigChunk + nnz / kBi
 
 // Byte offsets of the arrays of a graph inside its device buffer, and of the
 // build's temporaries inside the build scratch; both depend on (n, p,
-// n_tuples) only.
+// n_tuples) only, and the scratch on whether the entries are sorted as a whole
+// (where `sort` allows it and there are neither few nor very many of them).
 struct GraphLayout {
     int64_t n, P, R, W, B, nnz, ntile;
     // graph buffer
     int64_t row_ptr, col_base, col, dir, deg, pull_off, pull_col, head, live, qoff, small, graph_bytes;
     // build scratch
     bool sorted;  // entries sorted as a whole (radix.hip)
-    int64_t radix, row_start, cnt, sums, nnzb, misc, queues, scan, scratch_bytes;
+    int64_t radix, cnt, sums, nnzb, misc, queues, scan, scratch_bytes;
 };
-int graph_layout(int64_t n, int64_t n_tuples, int32_t p, GraphLayout *out);
+int graph_layout(int64_t n, int64_t n_tuples, int32_t p, GraphLayout *out, bool sort = true);
 
 }  // namespace csbfs
 
@@ -90,12 +91,12 @@ int sort_rows_desc(uint32_t *col, uint32_t *tmp, const int32_t *row_ptr, const i
                    int32_t P, int64_t nnz, int64_t *queues, unsigned long long *q_count, int32_t *err,
                    bool sorted, hipStream_t st);
 // Every entry of the tuples to its sorted place in col (all blocks, rows in
-// decreasing id order), and each non-empty row's first and last place + 1;
-// *err is set by a tuple id outside [0, n). `keys` holds 8 bytes an entry and
-// may overlap col.
+// decreasing id order), and the place after the last entry of a non-empty row u
+// of block b to row_end[b * (n / P + 1) + u]; *err is set by a tuple id outside
+// [0, n). `keys` holds 8 bytes an entry and may overlap col.
 int64_t radix_scratch_bytes(int64_t nnz);
 int sort_entries(const int64_t *src, const int64_t *dst, int64_t n_tuples, int64_t n, int32_t P, void *scratch,
-                 void *keys, uint32_t *col, int32_t *row_start, int32_t *row_end, int32_t *err, hipStream_t st);
+                 void *keys, uint32_t *col, int32_t *row_end, int32_t *err, hipStream_t st);
 // off[v] = sum of deg[u] for u < v (off has n + 1 entries; off[n] = total);
 // tile_sum holds scan_tiles(n) entries of scratch.
 int64_t scan_tiles(int64_t n);

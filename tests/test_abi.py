@@ -195,3 +195,22 @@ def test_search_config_layout_matches_header():
     names = re.findall(r"\b(?:uint32_t|int32_t|float)\s+(\w+);", body)
     assert names == [f[0] for f in csbfs.SearchConfig._fields_]
     assert ctypes.sizeof(csbfs.SearchConfig) == 24 and ctypes.sizeof(csbfs.Sizes) == 32
+
+
+def _counting_scratch(n, m, p):
+    """What the header says is always enough for a build that counts."""
+    return 4 * p * n + p * n // 64 + 5 * m // 8 + 16 * p * p + 8192
+
+
+@pytest.mark.parametrize("n,m,p", [(64, 1, 1), (64 * 64, 1000, 64), (3 << 20, 100000, 1), (1 << 24, (1 << 17) - 1, 64),
+                                   (1 << 30, (1 << 30) + 1, 4), (3 << 27, 1 << 28, 64), (1 << 26, 1 << 30, 8),
+                                   (1 << 20, 1 << 24, 4), (1 << 12, 1 << 17, 1)])
+def test_build_scratch_stays_near_the_graph(n, m, p):
+    """Graph and scratch of a build fit wherever the counting build's do, but
+    for 8.25 bytes an entry of at most 2^31 that are sorted (17 GiB)."""
+    from paper_1208_5542_amd import csbfs
+    scratch = csbfs.layout_query(n, m, p)["build_scratch_bytes"]
+    if 1 << 18 <= 2 * m <= 1 << 31:
+        assert scratch <= 8.51 * 2 * m + 16 * p * p + p * n // 64 + (1 << 18)
+    else:
+        assert scratch <= _counting_scratch(n, m, p)
