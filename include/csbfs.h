@@ -36,7 +36,8 @@
  *     allocate those same buffers themselves (hipMalloc) and free them in
  *     csbfs_graph_free and csbfs_engine_free. Buffers of graphs and of their
  *     builds that are freed are kept for later builds, up to 2 GiB per process,
- *     and go back to the device when an allocation of the library needs them.
+ *     and go back to the device when an allocation of the library needs them
+ *     or csbfs_trim is called.
  *     The codec calls allocate nothing.
  *
  * The WAH-64 stream format (Sec. IV, Table 3 and the 32-bit example in the
@@ -138,6 +139,14 @@ int csbfs_graph_build_into(const int64_t *src, const int64_t *dst, int64_t n_tup
  * csbfs_graph_build_into leaves the caller's buffer alone and makes no HIP
  * call. NULL is accepted. */
 int csbfs_graph_free(csbfs_graph *g);
+
+/*
+ * Give back (hipFree) the device memory that the library keeps of freed graphs
+ * and finished builds for later builds, on every device: for a program whose
+ * other allocations need it. No memory of a live object is touched.
+ * Thread-safe. Errors: none.
+ */
+int csbfs_trim(void);
 
 typedef struct csbfs_graph_info {
     int64_t n;              /* vertices */

@@ -90,6 +90,7 @@ def lib():
                              ctypes.c_size_t)
     sig = {
         "csbfs_version": ([], ctypes.c_int),
+        "csbfs_trim": ([], ctypes.c_int),
         "csbfs_strerror": ([ctypes.c_int], ctypes.c_char_p),
         "csbfs_last_error": ([], ctypes.c_char_p),
         "csbfs_graph_build": ([vp, vp, i64, i64, i32, vp, ctypes.POINTER(vp)], ctypes.c_int),
@@ -177,6 +178,12 @@ def _leave(stream):
 
 def version() -> int:
     return lib().csbfs_version()
+
+
+def trim() -> None:
+    """Give back the device memory kept of freed graphs and finished builds
+    (for torch's allocations, which cannot reclaim it themselves)."""
+    _check(lib().csbfs_trim(), "csbfs_trim")
 
 
 def strerror(status: int) -> str:

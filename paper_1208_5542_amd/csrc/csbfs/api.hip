@@ -121,6 +121,11 @@ void device_release(int device, const DeviceBlock &b) {
 
 extern "C" int csbfs_version(void) { return CSBFS_VERSION; }
 
+extern "C" int csbfs_trim(void) {
+    csbfs::device_trim();
+    return CSBFS_OK;
+}
+
 extern "C" const char *csbfs_strerror(int status) {
     switch (status) {
         case CSBFS_OK: return "ok";

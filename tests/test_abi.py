@@ -214,3 +214,7 @@ def test_build_scratch_stays_near_the_graph(n, m, p):
         assert scratch <= 8.51 * 2 * m + 16 * p * p + p * n // 64 + (1 << 18)
     else:
         assert scratch <= _counting_scratch(n, m, p)
+
+
+def test_trim_with_nothing_kept(lib):
+    assert lib.csbfs_trim() == 0
