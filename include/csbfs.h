@@ -156,7 +156,8 @@ typedef struct csbfs_graph_info {
     int64_t n_tuples;       /* input tuples */
     int64_t nnz;            /* adjacency entries over all blocks = 2 * n_tuples */
     int64_t max_block_nnz;  /* largest sub-block */
-    int64_t device_bytes;   /* device memory held by the graph */
+    int64_t device_bytes;   /* device memory held by the graph (csbfs_graph_build may reuse a
+                               kept buffer up to a quarter larger than it needs) */
 } csbfs_graph_info;
 
 /* Sizes of a built graph (host call, no device work). */

@@ -606,6 +606,7 @@ extern "C" int csbfs_graph_build(const int64_t *src, const int64_t *dst, int64_t
         return rc;
     }
     (*out)->owned = gm;
+    (*out)->device_bytes = (int64_t)gm.bytes;  // a kept block may be a quarter larger than asked
     return CSBFS_OK;
 }
 

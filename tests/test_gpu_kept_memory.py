@@ -41,3 +41,19 @@ def test_trim_gives_kept_blocks_back():
     csbfs.trim()  # nothing kept
     g = csbfs.Graph(src, dst, 1 << 20, 4)
     assert g.info.nnz == 1 << 25
+
+
+def test_device_bytes_of_a_graph_in_a_reused_block():
+    from paper_1208_5542_amd import csbfs
+    n, m = 1 << 20, 1 << 23
+    src, dst = _tuples(n, m)
+    a = csbfs.Graph(src, dst, n, 2)
+    assert a.info.device_bytes == csbfs.layout_query(n, m, 2)["graph_bytes"]
+    a.close()
+    less = m - m // 10
+    free = torch.cuda.mem_get_info()[0]
+    b = csbfs.Graph(src[:less], dst[:less], n, 2)
+    assert torch.cuda.mem_get_info()[0] == free  # both blocks were kept ones
+    assert b.info.device_bytes == a.info.device_bytes > csbfs.layout_query(n, less, 2)["graph_bytes"]
+    c = csbfs.Graph(src[:less], dst[:less], n, 2, memory="caller")
+    assert c.info.device_bytes == csbfs.layout_query(n, less, 2)["graph_bytes"]
