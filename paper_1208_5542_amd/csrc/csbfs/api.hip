@@ -1,8 +1,8 @@
 // Version, status strings, the thread-local last-error message, and the device
 // blocks of graphs and builds.
+#include <algorithm>
 #include <mutex>
 #include <string>
-#include <vector>
 
 #include "common.hpp"
 
@@ -27,31 +27,38 @@ int hip_fail(hipError_t err, const char *what, const char *file, int line) {
 
 namespace {
 
+// Kept blocks, oldest first. A fixed array: giving a block back must not
+// allocate, as no exception may leave csbfs_graph_free.
 struct Kept {
     int device;
     DeviceBlock b;
 };
+constexpr int kKeptMax = 64;
 std::mutex g_kept_mu;
-std::vector<Kept> g_kept;  // oldest first
+Kept g_kept[kKeptMax];
+int g_kept_count = 0;
 size_t g_kept_bytes = 0;
 
-// Gives back the oldest kept blocks until at most `limit` bytes are kept (the
-// lock is held).
-void trim(size_t limit) {
-    size_t k = 0;
-    while (k < g_kept.size() && g_kept_bytes > limit) {
-        (void)hipFree(g_kept[k].b.p);
-        g_kept_bytes -= g_kept[k].b.bytes;
-        ++k;
-    }
-    g_kept.erase(g_kept.begin(), g_kept.begin() + (long)k);
+// Takes entry k out (the lock is held).
+DeviceBlock take_out(int k) {
+    const DeviceBlock b = g_kept[k].b;
+    g_kept_bytes -= b.bytes;
+    std::copy(g_kept + k + 1, g_kept + g_kept_count, g_kept + k);
+    --g_kept_count;
+    return b;
+}
+
+// Gives back the oldest kept blocks until at most `limit` bytes in `count`
+// blocks are kept (the lock is held).
+void trim(size_t limit, int count) {
+    while (g_kept_bytes > limit || g_kept_count > count) (void)hipFree(take_out(0).p);
 }
 
 }  // namespace
 
 void device_trim() {
     std::lock_guard<std::mutex> lk(g_kept_mu);
-    trim(0);
+    trim(0, 0);
 }
 
 int device_malloc(void **p, size_t bytes) {
@@ -74,17 +81,15 @@ int device_take(size_t bytes, DeviceBlock *out) {
     CSBFS_HIP(hipGetDevice(&dev));
     {
         std::lock_guard<std::mutex> lk(g_kept_mu);
-        size_t best = g_kept.size();
-        for (size_t k = 0; k < g_kept.size(); ++k) {
+        int best = -1;
+        for (int k = 0; k < g_kept_count; ++k) {
             const Kept &x = g_kept[k];
             if (x.device == dev && x.b.bytes >= bytes && x.b.bytes <= bytes + bytes / 4 &&
-                (best == g_kept.size() || x.b.bytes < g_kept[best].b.bytes))
+                (best < 0 || x.b.bytes < g_kept[best].b.bytes))
                 best = k;
         }
-        if (best < g_kept.size()) {
-            *out = g_kept[best].b;
-            g_kept_bytes -= out->bytes;
-            g_kept.erase(g_kept.begin() + (long)best);
+        if (best >= 0) {
+            *out = take_out(best);
             return CSBFS_OK;
         }
     }
@@ -100,8 +105,8 @@ void device_give(const DeviceBlock &b) {
         return;
     }
     std::lock_guard<std::mutex> lk(g_kept_mu);
-    trim(kKeptBytes - b.bytes);
-    g_kept.push_back(Kept{dev, b});
+    trim(kKeptBytes - b.bytes, kKeptMax - 1);
+    g_kept[g_kept_count++] = Kept{dev, b};
     g_kept_bytes += b.bytes;
 }
 
