@@ -1398,6 +1398,7 @@ constexpr int64_t hdr_words(int64_t P) { return kLine + ((P + 1) / 2 + kLine - 1
 }  // namespace
 }  // namespace csbfs
 
+#include "small_rule.hpp"
 #include "bfs_small.hpp"
 
 namespace csbfs {
@@ -1671,18 +1672,11 @@ int finish_search(const SearchLayout &y, const std::vector<unsigned long long> &
     return CSBFS_OK;
 }
 
-// Searches that one workgroup makes in one launch (small_search_kernel): the
-// state fits LDS and the adjacency is short enough for one CU. The limit lies
-// where the level-by-level kernels' time (220 to 260 us, launches mostly) is
-// reached: with 2^19 entries (R-MAT scale 14) 128 us, with 580k (uniform,
-// 16128 vertices) 196 us against 251, with 2^20 222 us against 234 (R-MAT
-// scale 15) and 284 against 257 (uniform, 25600 vertices). The dense
-// evaluation, per-kernel timing, a binned push and a fixed encoder segment
-// ask for the level-by-level kernels.
-constexpr int64_t kSmallNnz = int64_t(3) << 18;
-bool small_search(const SearchLayout &y, const csbfs_graph *g, const SmallLds &l, bool dense, bool timing) {
-    return !dense && !timing && y.nbins == 0 && !y.enc_fixed && g->nnz <= kSmallNnz && g->n <= (1 << 15) &&
-           8 * (int64_t)l.total <= 160 * 1024 - 1024;
+// Searches in one launch: where the state and the streams allow (small_fits),
+// unless the dense evaluation, per-kernel timing, a binned push or a fixed encoder
+// segment asks for the level-by-level kernels.
+bool small_search(const SearchLayout &y, const csbfs_graph *g, bool dense, bool timing) {
+    return !dense && !timing && y.nbins == 0 && !y.enc_fixed && small_fits(g->n, g->P, g->nnz);
 }
 
 constexpr int kEvPerLevel2 = kEvPerLevel;
@@ -1731,8 +1725,8 @@ int run_search(const csbfs_graph *g, const SearchLayout &y, const SearchState &w
     };
     auto levels_wanted = [&](int64_t nl) { return std::min<int64_t>(stats_cap, std::min<int64_t>(nl, y.L)); };
     int64_t nl = 0;
-    const SmallLds sl = small_lds(n, P);
-    if (small_search(y, g, sl, dense, timing)) {
+    if (small_search(y, g, dense, timing)) {
+        const SmallLds sl = small_lds(n, P);
         SmallArgs sa{sl, (int32_t)n, (int32_t)R, (int32_t)W, (int32_t)P, (int32_t)root, g->row_ptr, g->col_base, g->col,
                      (y.flags & CSBFS_FLAG_NO_SIEVE) ? nullptr : g->dir, g->deg, g->live, g->pull_off, g->pull_col,
                      g->head, level, parent, w.arena, y.cap, keep ? S * y.cap : 0,

@@ -5,7 +5,7 @@
 // by workgroup barriers instead of launches, and its atomics are LDS atomics.
 // Messages are the same: stream i -> j is sieved, WAH-64 encoded by one wave
 // (written to the arena like any stream) and decoded by that wave into view
-// (j, i).
+// (j, i). small_rule.hpp says which searches.
 //
 // Bound by latency, and by one CU's issue rate towards the upper limit: the
 // searches this serves touch a few 10^5 adjacency entries in 6 to 8 levels,
@@ -15,40 +15,13 @@
 namespace csbfs {
 namespace {
 
-constexpr int kSmallThreads = 1024;
-constexpr int kSmallWaves = kSmallThreads / 64;
 constexpr int kSmallLong = 256;    // longer rows are pushed by the whole workgroup
-constexpr int kSmallQueue = 512;   // of them per level (a row that finds no slot stays with its wave)
 constexpr int kSmallUnroll = 4;    // adjacency entries in flight per lane
 
 struct SmallItem {
     int32_t col, len, u, vbase;
 };
-
-// Places in LDS, in 64-bit words.
-struct SmallLds {
-    int32_t pi, nb, view, buf, nbuf, buf_words, par, queue, total;
-};
-inline SmallLds small_lds(int64_t n, int64_t P) {
-    const int64_t words = n / 64, R = n / P, S = P * P;
-    SmallLds l{};
-    int64_t o = 0;
-    auto take = [&o](int64_t w) {
-        const int64_t at = o;
-        o += w;
-        return (int32_t)at;
-    };
-    l.nbuf = (int32_t)(S < kSmallWaves ? S : kSmallWaves);
-    l.buf_words = (int32_t)(R / 64 + 1 + wah_cap(R));  // a sieved piece and its stream
-    l.pi = take(words);
-    l.nb = take(2 * words);
-    l.view = take(P * words);
-    l.buf = take((int64_t)l.nbuf * l.buf_words);
-    l.par = take((n + 1) / 2);
-    l.queue = take(2 * kSmallQueue);
-    l.total = (int32_t)o;
-    return l;
-}
+static_assert(sizeof(SmallItem) == 16, "two words of the queue's LDS");
 
 struct SmallArgs {
     SmallLds l;
