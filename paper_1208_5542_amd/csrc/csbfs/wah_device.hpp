@@ -547,7 +547,11 @@ __device__ void fill_ones_lds(unsigned long long *buf, int64_t lo, int64_t hi) {
 // touch, need global atomics. Bound by memory: the stream is read
 // once and dst read and written once. Chunks whose fills span more groups OR
 // straight into dst.
-constexpr int dec_lds_groups(int t) { return t == 1 ? 2 * kDecChunk : t * kDecChunk + kDecChunk; }
+// Groups of a chunk that LDS holds: two a word, so that a stream whose every
+// literal is followed by a fill of up to three groups still fits (four
+// workgroups per CU in either case). With one and a half a word for kT = 2, streams
+// of 2^28 bits with 1.5 to 2 groups a word took 57 to 71 us, now 50 to 53.
+constexpr int dec_lds_groups(int t) { return 2 * t * kDecChunk + 64; }
 
 template <int kT, bool kZeroed, class Start>
 __device__ __forceinline__ void dec_chunk(const uint64_t *words, int64_t nw, int64_t G, int64_t r, int64_t c,
