@@ -295,6 +295,32 @@ __device__ void small_update(const SmallArgs &a, SmallShared &sh, uint64_t *pi, 
     }
 }
 
+// or_bits and fill_ones on words in LDS.
+__device__ __forceinline__ void or_bits_lds(unsigned long long *buf, int64_t bit, uint64_t v, int nbits) {
+    const int64_t q = bit >> 6;
+    const int sh = (int)(bit & 63);
+    const uint64_t lo = v << sh;
+    if (lo) atomicOr(&buf[q], (unsigned long long)lo);
+    if (sh + nbits > 64) {
+        const uint64_t hi = v >> (64 - sh);
+        if (hi) atomicOr(&buf[q + 1], (unsigned long long)hi);
+    }
+}
+
+__device__ void fill_ones_lds(unsigned long long *buf, int64_t lo, int64_t hi) {
+    int64_t q0 = lo >> 6, q1 = (hi - 1) >> 6;
+    for (int64_t q = q0; q <= q1; ++q) {
+        const int64_t a = lo > q * 64 ? lo - q * 64 : 0;
+        const int64_t e = hi < q * 64 + 64 ? hi - q * 64 : 64;
+        if (a == 0 && e == 64) {
+            buf[q] = ~0ull;  // a whole word inside one fill has no other writer
+        } else {
+            const uint64_t m = (e == 64 ? ~0ull : ((1ull << e) - 1)) & ~((1ull << a) - 1);
+            atomicOr(&buf[q], (unsigned long long)m);
+        }
+    }
+}
+
 // Stream i -> j of the frontier piece f_i by one wave: sieve, encode, store,
 // decode into view (j, i). `buf` holds the sieved piece and the stream.
 __device__ void small_stream(const SmallArgs &a, SmallShared &sh, int32_t i, int32_t j, const uint64_t *nb,

@@ -101,9 +101,11 @@ struct WahBatch {
     int32_t planes;             // 0 or 1 for one search
     int64_t bits_plane_stride;
     int64_t dst_plane_stride;
-    // encoder scratch, zero between launches (each launch leaves it zero):
-    // per (stream, segment) look-back words; per stream a segment ticket and
-    // a count of finished segments
+    // encoder scratch: per (stream, segment) look-back words, per stream the
+    // segments started. Both are zero before a stream's first launch and left as
+    // they are by every launch: the tickets count on, and a word's parity tells
+    // this launch's from the last one's. One set per stream at a time; a stream of
+    // one segment takes no ticket and reads no look-back word.
     unsigned long long *look;   // device [S * nseg]
     uint32_t *ticket;           // device [kTicketStride * S]
     int64_t nseg;

@@ -261,7 +261,7 @@ extern "C" int csbfs_wah_encode_noalloc(const uint64_t *bits, const uint64_t *ma
     const WsLayout l = ws_layout(nbits);
     char *ws = (char *)ptr;
     // look-back words and tickets start at zero; the previous call on this
-    // device left them zero unless it failed, so clear them every time
+    // device left its own there. A stream of one segment reads neither.
     const int64_t words = (int64_t)((l.dec_look - l.look) / 4);
     if (enc_segments(nbits) > 1) {
         hipLaunchKernelGGL(zero_words_kernel, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, st,

@@ -75,9 +75,6 @@ __device__ T block_reduce(T v, Op op, T identity) {
 struct SumI64 {
     __device__ long long operator()(long long a, long long b) const { return a + b; }
 };
-struct MinI32 {
-    __device__ int operator()(int a, int b) const { return a < b ? a : b; }
-};
 struct SumI32 {
     __device__ int operator()(int a, int b) const { return a + b; }
 };
@@ -504,32 +501,6 @@ __device__ void fill_ones(uint64_t *dst, int64_t lo, int64_t hi) {
         } else {
             const uint64_t m = (e == 64 ? ~0ull : ((1ull << e) - 1)) & ~((1ull << a) - 1);
             atomicOr((unsigned long long *)&dst[q], (unsigned long long)m);
-        }
-    }
-}
-
-// The same two helpers on words in LDS.
-__device__ __forceinline__ void or_bits_lds(unsigned long long *buf, int64_t bit, uint64_t v, int nbits) {
-    const int64_t q = bit >> 6;
-    const int sh = (int)(bit & 63);
-    const uint64_t lo = v << sh;
-    if (lo) atomicOr(&buf[q], (unsigned long long)lo);
-    if (sh + nbits > 64) {
-        const uint64_t hi = v >> (64 - sh);
-        if (hi) atomicOr(&buf[q + 1], (unsigned long long)hi);
-    }
-}
-
-__device__ void fill_ones_lds(unsigned long long *buf, int64_t lo, int64_t hi) {
-    int64_t q0 = lo >> 6, q1 = (hi - 1) >> 6;
-    for (int64_t q = q0; q <= q1; ++q) {
-        const int64_t a = lo > q * 64 ? lo - q * 64 : 0;
-        const int64_t e = hi < q * 64 + 64 ? hi - q * 64 : 64;
-        if (a == 0 && e == 64) {
-            buf[q] = ~0ull;  // a whole word inside one fill has no other writer
-        } else {
-            const uint64_t m = (e == 64 ? ~0ull : ((1ull << e) - 1)) & ~((1ull << a) - 1);
-            atomicOr(&buf[q], (unsigned long long)m);
         }
     }
 }
