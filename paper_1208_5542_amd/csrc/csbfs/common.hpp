@@ -29,7 +29,8 @@ int hip_fail(hipError_t err, const char *what, const char *file, int line);
 // Device blocks that the library allocates for graphs and their builds. A
 // block that is let go is kept for the next taker of about its size, as long
 // as the kept ones stay below kKeptBytes per process; the rest go back to the
-// device, the oldest first, and all of them when an allocation fails. A
+// device, the oldest first, and all of them when an allocation fails or
+// csbfs_trim is called. A
 // hipFree of 64 MB or more takes 300 us or more, and memory freshly given back
 // is cleared at about 35 GB/s before it can be had again: builds of a graph of
 // 2^20 vertices one after another took 25 ms each waiting for it, now 2.4.

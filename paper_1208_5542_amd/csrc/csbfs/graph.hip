@@ -198,7 +198,7 @@ __global__ __launch_bounds__(kThreads) void k_degree(const int32_t *row_ptr, int
 
 // Consistency of a built graph: the largest column id (must be below R) and
 // the degree total (must equal nnz). One pair of atomics per workgroup (one
-// per wave took 392 us of atomics on two addresses at scale 20; now 64).
+// per wave took 392 us of atomics on two addresses at scale 20; now 72).
 __global__ __launch_bounds__(kThreads) void k_check(const uint32_t *col, int64_t nnz, const int32_t *deg, int64_t n,
                                                     unsigned long long *out) {
     __shared__ uint32_t wmax[kThreads / 64];
@@ -348,12 +348,14 @@ __global__ void k_live(const int32_t *deg, int64_t n, uint64_t *live) {
 }
 
 // Builds of this many entries sort them (radix.hip) instead of counting,
-// scattering and sorting rows. R-MAT, 4 x 4, in us (sort, else): 2^17 entries
-// 313, 321; 2^18 324, 412; 2^20 342, 533; 2^25 1820, 5850; 2^31 (8 x 8) 145 ms,
-// 397. Above, the places do not fit 32 bits.
+// scattering and sorting rows. R-MAT, 4 x 4, in us (sort, counting), in memory
+// of the caller's: 2^17 entries 313, 321; 2^18 313, 369; 2^20 358, 582; 2^25
+// 1780, 6136; 2^31 (8 x 8) 148 ms, 406. (csbfs_graph_build adds its allocations:
+// above the 2 GiB that are kept, about 30 ms a GiB where the memory was given back
+// just before and is cleared first.) Above 2^31, the places do not fit 32 bits.
 // The sort needs 8.25 bytes of scratch an entry, where counting needs 4 p n and
-// a quarter byte an entry: at 2^31 entries on the 8 x 8 grid 16.5 GiB against
-// 2.5. A build that cannot have the sort's scratch counts instead.
+// a quarter byte an entry: at 2^31 entries on the 8 x 8 grid 17.0 GiB against
+// 2.6. A build that cannot have the sort's scratch counts instead.
 constexpr int64_t kSortMin = int64_t(1) << 18, kSortMax = int64_t(1) << 31;
 
 constexpr int kMiscWords = 64;  // build flags and counters: err, sort queue counts, check, big items

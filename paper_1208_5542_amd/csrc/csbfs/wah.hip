@@ -17,7 +17,7 @@ __global__ __launch_bounds__(kEncThreads) void wah_encode_kernel(WahBatch b) {
 // A stream from elsewhere, in one pass over it (a pass that summed every
 // chunk's groups first, two clears and a copy of the length from the host made
 // it 50 us for the smallest streams, now 30 with the caller's read of the
-// status; 2^28 bits 89 us, now 78). Chunks are taken in ticket order, so every awaited
+// status; 2^28 bits 90 us, now 75). Chunks are taken in ticket order, so every awaited
 // one runs; a chunk publishes its group total (state 1), then the total
 // through it (state 2), each in one 64-bit word whose top two bits are the
 // state. Totals above G (an invalid stream) are cut off at G + 1.
