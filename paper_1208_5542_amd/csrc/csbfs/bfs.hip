@@ -1764,6 +1764,8 @@ int run_search(const csbfs_graph *g, const SearchLayout &y, const SearchState &w
                 w.marks[0], 2 * y.nmarks, root, one_word, one_word + 4, (const int32_t *)g->deg, w.dstate, dir0};
     int64_t fill_items = n > view_words ? n : view_words;
     fill_items = fill_items > y.look_bytes / 4 ? fill_items : y.look_bytes / 4;
+    // the records too: 65536 kept levels at p = 4 are 50 MB of them
+    fill_items = std::max(fill_items, y.counters_bytes / 4);
     hipLaunchKernelGGL(seed_kernel, dim3(grid_for(fill_items, 256, 8192)), dim3(256), 0, st, sa);
     CSBFS_HIP(hipGetLastError());
 
