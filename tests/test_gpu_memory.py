@@ -189,3 +189,20 @@ def test_row_sort_every_length_class():
             ref = adj.alg3(p, V, root)
             assert (r.level.cpu().numpy() == ref.level).all()
             assert (r.parent.cpu().numpy() == ref.parent).all()
+
+
+@pytest.mark.parametrize("mailbox", [True, False])
+@pytest.mark.parametrize("max_levels", [1, 2, 63, 64])
+def test_level_count_past_the_kept_levels(max_levels, mailbox):
+    """Levels that share the last record are counted all the same, also where
+    the host reads each level's size from that record."""
+    from paper_1208_5542_amd import csbfs
+    n, p = 64 * 600, 3
+    src = np.arange(64, dtype=np.int64)
+    g = csbfs.Graph(_dev(src), _dev(src + 1), n, p)
+    cfg = csbfs.search_config(max_levels=max_levels, segment_groups=1024)  # the level-by-level kernels
+    eng = csbfs.WorkspaceSearch(g, cfg, mailbox=mailbox)
+    for root, levels in ((0, 65), (40, 41), (100, 1)):
+        r = eng.bfs(root)
+        assert r.n_levels == levels == int(r.level.max()) + 1
+        assert [s["frontier"] for s in r.stats[1:]] == [1 + (root > 0 and k <= 24) for k in range(1, min(levels, max_levels))]
