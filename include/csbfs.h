@@ -143,7 +143,8 @@ int csbfs_graph_free(csbfs_graph *g);
 /*
  * Give back (hipFree) the device memory that the library keeps of freed graphs
  * and finished builds for later builds, on every device: for a program whose
- * other allocations need it. No memory of a live object is touched.
+ * other allocations need it, or before hipDeviceReset, which would leave the
+ * library with memory that is gone. No memory of a live object is touched.
  * Thread-safe. Errors: none.
  */
 int csbfs_trim(void);
@@ -647,6 +648,8 @@ int64_t csbfs_wah_noalloc_max_bits(void);
  * (device uint64[ceil(nbits/64)]; zero it first for a plain decode).
  *   status  device int32[1]: set to 0 if the stream is a valid encoding of
  *           exactly nbits bits, non-zero otherwise (dst then unspecified).
+ *   workspace  as for csbfs_wah_encode: one call at a time per workspace.
+ * status, dst and workspace are in use until the work on `stream` is done.
  * Asynchronous. Errors: EINVAL, ENOSPACE, EHIP.
  */
 int csbfs_wah_decode_or(const uint64_t *words, int64_t n_words, int64_t nbits, uint64_t *dst,
