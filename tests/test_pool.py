@@ -22,4 +22,6 @@ def test_device_block_pool(tmp_path, kind):
                     os.path.join(REPO, "include"), os.path.join(HERE, "pool_check.cpp"), "-o", exe], check=True)
     env = dict(os.environ, ASAN_OPTIONS="detect_leaks=0:verify_asan_link_order=0")
     r = subprocess.run([exe], capture_output=True, text=True, env=env, timeout=120)
+    if "unexpected memory mapping" in r.stderr:  # a kernel whose address randomization this sanitizer does not know
+        pytest.skip(r.stderr.strip())
     assert r.returncode == 0 and "ok" in r.stdout, r.stdout + r.stderr
